@@ -22,7 +22,7 @@ enum Slot {
   S_C, S_C1, S_ARRIVE, S_MTMP, S_OV0, S_OP0, S_OI0, S_OV1, S_OP1, S_OI1, S_FV, S_FP, S_FI, S_CTL,
   S_IMIN, S_ITHR, S_IROUNDS, S_ISCAN, S_DEGEN, S_LVL, S_FLAG, S_SPRED, S_ISTAT,
   S_GTAB, S_ITAB,
-  S_BK_KA, S_BK_KB, S_BK_VA, S_BK_VB, S_BK_HIST, S_BK_TAIL, S_BK_STATUS,
+  S_BK_COLS, S_BK_HIST, S_BK_TAIL, S_BK_HEAD, S_BK_DEG, S_BK_STATUS,
   S_BW_ACC, S_BW_LV, S_BW_LI, S_BW_LOFF, S_BW_CTL, S_BW_GOFF, S_BW_GINST, S_BW_EBASE,
   S_BW_CS, S_BW_LACC,
   S_TRACE, S_FLAGS, S_PART, S_D64, S_FX, S_OX0, S_OX1, S_LV0, S_LV1, S_DR, S_INSTOF, S_IDEAD,
@@ -337,14 +337,19 @@ SolverCopy solver_copy(const sssp_csr *g) {
 // Sort temporaries of the builder for n vertices and m edges.
 sssp_status build_temps(DevWS &ws, int32_t n, int32_t m, BuildTemps *t) {
   sssp_status s;
-  const size_t M = (size_t)(m > n ? m : n);
-  if ((s = ws_arr(ws, S_BK_KA, M, &t->ka))) return s;
-  if ((s = ws_arr(ws, S_BK_KB, M, &t->kb))) return s;
-  if ((s = ws_arr(ws, S_BK_VA, M, &t->va))) return s;
-  if ((s = ws_arr(ws, S_BK_VB, M, &t->vb))) return s;
+  // eight sort columns; their starts keep the allocation's alignment
+  const size_t M = (((size_t)(m > n ? m : n) + 63) & ~(size_t)63);
+  int32_t *cols;
+  if ((s = ws_arr(ws, S_BK_COLS, 8 * M, &cols))) return s;
+  for (int k = 0; k < 4; ++k) {
+    t->a[k] = cols + (size_t)k * M;
+    t->b[k] = cols + (size_t)(4 + k) * M;
+  }
   if ((s = ws_arr(ws, S_BK_TAIL, (size_t)(m > 0 ? m : 1), &t->tail))) return s;
-  if ((s = ws_arr(ws, S_BK_HIST, build_hist_entries(m > n ? m : n), &t->hist))) return s;
-  if ((s = ws_arr(ws, S_BK_STATUS, 4, &t->status))) return s;
+  if ((s = ws_arr(ws, S_BK_HEAD, (size_t)(m > 0 ? m : 1), &t->head))) return s;
+  if ((s = ws_arr(ws, S_BK_DEG, (size_t)n, &t->deg))) return s;
+  if ((s = ws_arr(ws, S_BK_HIST, build_hist_entries(n, m), &t->hist))) return s;
+  if ((s = ws_arr(ws, S_BK_STATUS, kBuildStatus, &t->status))) return s;
   return SSSP_OK;
 }
 
@@ -612,10 +617,16 @@ sssp_status sssp_build_csr(int32_t n, int32_t m, sssp_dtype dtype, sssp_order or
   int32_t *in_w = arr(B_IN_W), *out_wmin = arr(B_OUT_WMIN);
   BuildTemps t;
   if ((s = build_temps(ws, n, m, &t))) return s;
-  HIPCHK(hipMemsetAsync(t.status, 0, 4 * sizeof(int32_t), stream));
-  HIPCHK(launch_validate(n, m, f32, src, dst, (const int32_t *)w, t.status, stream));
-  int32_t hs[4];
-  HIPCHK(hipMemcpyAsync(hs, t.status, sizeof(hs), hipMemcpyDeviceToHost, stream));
+  void *hp;
+  if ((s = pinned_get(ws, kBuildStatus * sizeof(int32_t), &hp))) return s;
+  const int32_t *hs = (const int32_t *)hp;
+  HIPCHK(hipMemsetAsync(t.status, 0, kBuildStatus * sizeof(int32_t), stream));
+  HIPCHK(launch_validate(n, m, f32, src, dst, (const int32_t *)w, nullptr, t.status, stream));
+  // (safe on bad endpoints: one read-back serves both verdicts)
+  HIPCHK(launch_build(n, m, src, dst, (const int32_t *)w, out_off, out_dst, out_w, in_off,
+                      in_src, in_eid, in_w, perm, t, stream));
+  HIPCHK(hipMemcpyAsync(hp, t.status, kBuildStatus * sizeof(int32_t), hipMemcpyDeviceToHost,
+                        stream));
   HIPCHK(hipStreamSynchronize(stream));
   if (hs[0] & 1) return SSSP_ERR_GRAPH;
   if (hs[0] & 2) return SSSP_ERR_WEIGHT;
@@ -640,8 +651,7 @@ sssp_status sssp_build_csr(int32_t n, int32_t m, sssp_dtype dtype, sssp_order or
   out->w_max = key_value(wkey_max, f32);
   out->w_min = m > 0 ? key_value(0x7fffffff - hs[3], f32) : 0.0;
   if (overflow_risk(out)) return SSSP_ERR_OVERFLOW;
-  HIPCHK(launch_build(n, m, f32, src, dst, (const int32_t *)w, out_off, out_dst, out_w, in_off,
-                      in_src, in_eid, in_w, out_wmin, perm, t, stream));
+  HIPCHK(launch_out_wmin(f32, n, m, hs[2], out_off, out_w, out_wmin, t, stream));
   SolverCopy c;
   memset(&c, 0, sizeof(c));
   c.out_off = out_off;
@@ -656,12 +666,7 @@ sssp_status sssp_build_csr(int32_t n, int32_t m, sssp_dtype dtype, sssp_order or
   c.out_rec = arr(B_S_OUT_REC);
   c.vin = arr(B_S_VIN);
   c.vrec = arr(B_S_VREC);
-  if (m > 0) {
-    HIPCHK(launch_degree(n, out_off, in_off, t, stream));
-    HIPCHK(hipMemcpyAsync(hs, t.status, sizeof(hs), hipMemcpyDeviceToHost, stream));
-    HIPCHK(hipStreamSynchronize(stream));
-    out->deg_max = hs[2];
-  }
+  if (m > 0) out->deg_max = hs[2];
   if (order != SSSP_ORDER_INPUT && m > 0) {
     const int32_t dmax = out->deg_max;
     // skewed: largest total degree >= 16 x the mean 2m/n
@@ -674,11 +679,13 @@ sssp_status sssp_build_csr(int32_t n, int32_t m, sssp_dtype dtype, sssp_order or
       c.out_w = arr(B_S_OUT_W);
       c.out_eid = arr(B_S_OUT_EID);
       c.out_wmin = arr(B_S_OUT_WMIN);
-      HIPCHK(launch_renumber(n, m, dmax, out_dst, out_w, out_wmin, c, t, stream));
+      HIPCHK(launch_renumber(n, m, dmax, out_off, in_off, in_src, in_w, in_eid, out_wmin, c, t,
+                             stream));
       out->order = SSSP_ORDER_DEGREE;
     }
   }
-  HIPCHK(launch_in_lists(n, m, wkey_max, out_off, out_dst, out_w, c, t, stream));
+  HIPCHK(launch_in_lists(n, m, wkey_max, hs[4], out_dst, in_off, in_src, in_eid, in_w, true, c, t,
+                         stream));
   HIPCHK(launch_vrec(n, c, stream));
   HIPCHK(launch_out_rec(m, c, stream));
   out->s_vrec = c.vrec;
@@ -725,11 +732,14 @@ sssp_status sssp_set_weights(sssp_csr *g, const void *w, void *stream_) {
   BuildTemps t;
   if ((s = build_temps(ws, g->n, g->m, &t))) return s;
   // validate before anything is written: on error the graph is unchanged
-  HIPCHK(hipMemsetAsync(t.status, 0, 4 * sizeof(int32_t), stream));
-  HIPCHK(launch_validate(g->n, g->m, f32, nullptr, nullptr, (const int32_t *)w, t.status,
-                         stream));
-  int32_t hs[4];
-  HIPCHK(hipMemcpyAsync(hs, t.status, sizeof(hs), hipMemcpyDeviceToHost, stream));
+  void *hp;
+  if ((s = pinned_get(ws, kBuildStatus * sizeof(int32_t), &hp))) return s;
+  const int32_t *hs = (const int32_t *)hp;
+  HIPCHK(hipMemsetAsync(t.status, 0, kBuildStatus * sizeof(int32_t), stream));
+  HIPCHK(launch_validate(g->n, g->m, f32, nullptr, nullptr, (const int32_t *)w, g->in_off,
+                         t.status, stream));
+  HIPCHK(hipMemcpyAsync(hp, t.status, kBuildStatus * sizeof(int32_t), hipMemcpyDeviceToHost,
+                        stream));
   HIPCHK(hipStreamSynchronize(stream));
   if (hs[0] & 2) {
     HIPCHK(hipEventRecord(ws.last, stream));
@@ -742,11 +752,11 @@ sssp_status sssp_set_weights(sssp_csr *g, const void *w, void *stream_) {
     return SSSP_ERR_OVERFLOW;
   }
   const SolverCopy c = solver_copy(g);
-  HIPCHK(launch_set_weights(g->n, g->m, f32, (const int32_t *)w, g->out_off, g->in_eid,
-                            (int32_t *)g->out_w, (int32_t *)g->in_w, (int32_t *)g->out_wmin, c,
-                            stream));
-  HIPCHK(launch_in_lists(g->n, g->m, hs[1], g->out_off, g->out_dst, (const int32_t *)g->out_w,
-                         c, t, stream));
+  HIPCHK(launch_set_weights(g->n, g->m, f32, g->deg_max, (const int32_t *)w, g->out_off,
+                            g->in_eid, (int32_t *)g->out_w, (int32_t *)g->in_w,
+                            (int32_t *)g->out_wmin, c, stream));
+  HIPCHK(launch_in_lists(g->n, g->m, hs[1], hs[4], g->out_dst, g->in_off, g->in_src, g->in_eid,
+                         (const int32_t *)g->in_w, false, c, t, stream));
   HIPCHK(launch_vrec(g->n, c, stream));  // out_wmin and the in-list heads changed
   HIPCHK(launch_out_rec(g->m, c, stream));  // the weights and the heads' out_wmin
   HIPCHK(hipStreamSynchronize(stream));

@@ -227,11 +227,14 @@ hipError_t launch_small(bool f32, const RoundArgs &a, int32_t *pred, const Kerne
 
 // ------------------------------------------------------------- builder
 struct BuildTemps {
-  int32_t *ka, *kb, *va, *vb;  // radix sort ping-pong, max(m, n) each
-  int32_t *hist;               // 256 * tiles (+ scan sums)
-  int32_t *tail;               // m: tail of each edge id
-  int32_t *status;             // [0] error flags, [1] max weight key, [2] max total degree
+  int32_t *a[4], *b[4];  // sort columns, max(m, n) each
+  int32_t *hist;         // digit counts per tile (build_hist_entries)
+  int32_t *tail;         // m: tails (by edge id, or by position in the copy's CSR)
+  int32_t *head;         // m: heads by CSC position
+  int32_t *deg;          // n: total degrees
+  int32_t *status;       // kBuildStatus words, see validate_kernel
 };
+constexpr int kBuildStatus = 8;
 // The solver's working copy of a graph (arrays in the build buffer).  In
 // the input numbering vid, rank, out_eid are null and out_* alias the CSR;
 // the in-lists are always a copy, ascending by weight.
@@ -245,36 +248,44 @@ struct SolverCopy {
   int32_t *vrec;  // 8 ints per vertex
   int32_t *vin;   // 4 ints per vertex: vrec's in_off, in_degree, lightest tail and weight
 };
-size_t build_hist_entries(int32_t m);
+size_t build_hist_entries(int32_t n, int32_t m);
+// in_off nullable: also the largest in-degree
 hipError_t launch_validate(int32_t n, int32_t m, bool f32, const int32_t *src,
-                           const int32_t *dst, const int32_t *w, int32_t *status,
-                           hipStream_t stream);
-hipError_t launch_build(int32_t n, int32_t m, bool f32, const int32_t *src, const int32_t *dst,
+                           const int32_t *dst, const int32_t *w, const int32_t *in_off,
+                           int32_t *status, hipStream_t stream);
+// CSR and CSC (out_wmin: launch_out_wmin); the degrees into t.deg, their
+// maxima into t.status[2] and [4]; the heads by CSC position into t.head
+hipError_t launch_build(int32_t n, int32_t m, const int32_t *src, const int32_t *dst,
                         const int32_t *w, int32_t *out_off, int32_t *out_dst, int32_t *out_w,
                         int32_t *in_off, int32_t *in_src, int32_t *in_eid, int32_t *in_w,
-                        int32_t *out_wmin, int32_t *perm, const BuildTemps &t,
-                        hipStream_t stream);
-// degrees into t.ka, their maximum into t.status[2]
-hipError_t launch_degree(int32_t n, const int32_t *out_off, const int32_t *in_off,
-                         const BuildTemps &t, hipStream_t stream);
-// vid, rank and the CSR copy in descending-degree order, from the built CSR
-// and the degrees left in t.ka by launch_degree (dmax: their maximum)
-hipError_t launch_renumber(int32_t n, int32_t m, int32_t dmax, const int32_t *out_dst,
-                           const int32_t *out_w, const int32_t *out_wmin, const SolverCopy &c,
+                        int32_t *perm, const BuildTemps &t, hipStream_t stream);
+// after launch_build (the tails in t.tail); deg_max: at least the largest out-degree
+hipError_t launch_out_wmin(bool f32, int32_t n, int32_t m, int32_t deg_max,
+                           const int32_t *out_off, const int32_t *out_w, int32_t *out_wmin,
                            const BuildTemps &t, hipStream_t stream);
-// the weight-ordered in-lists of the copy (c.rank null: input numbering);
-// wkey_max: the largest weight's bit pattern.  Overwrites t.tail.
-hipError_t launch_in_lists(int32_t n, int32_t m, int32_t wkey_max, const int32_t *out_off,
-                           const int32_t *out_dst, const int32_t *out_w, const SolverCopy &c,
+// vid, rank, both offset arrays and the CSR copy in descending-degree order,
+// from the built CSC and the degrees left in t.deg (dmax: their maximum);
+// the tails by position in the copy's CSR into t.tail
+hipError_t launch_renumber(int32_t n, int32_t m, int32_t dmax, const int32_t *out_off,
+                           const int32_t *in_off, const int32_t *in_src, const int32_t *in_w,
+                           const int32_t *in_eid, const int32_t *out_wmin, const SolverCopy &c,
                            const BuildTemps &t, hipStream_t stream);
+// the weight-ordered in-lists of the copy (c.vid null: input numbering) from
+// the CSC, or in degree order from the copy's CSR; wkey_max: the largest
+// weight's bit pattern; ideg_max: the largest in-degree; fresh: t.head and
+// t.tail are as launch_build and launch_renumber left them
+hipError_t launch_in_lists(int32_t n, int32_t m, int32_t wkey_max, int32_t ideg_max,
+                           const int32_t *out_dst, const int32_t *in_off, const int32_t *in_src,
+                           const int32_t *in_eid, const int32_t *in_w, bool fresh,
+                           const SolverCopy &c, const BuildTemps &t, hipStream_t stream);
 // the per-vertex records of the copy (after its offsets and out_wmin)
 hipError_t launch_vrec(int32_t n, const SolverCopy &c, hipStream_t stream);
 // c.out_rec from the working copy's out-lists and out_wmin (after launch_vrec's inputs are final)
 hipError_t launch_out_rec(int32_t m, const SolverCopy &c, hipStream_t stream);
 // new weights (validated by the caller) into the CSR/CSC, out_wmin and the
 // copy's out-lists; the copy's in-lists are rebuilt by launch_in_lists
-hipError_t launch_set_weights(int32_t n, int32_t m, bool f32, const int32_t *w,
-                              const int32_t *out_off, const int32_t *in_eid, int32_t *out_w,
+hipError_t launch_set_weights(int32_t n, int32_t m, bool f32, int32_t deg_max,
+                              const int32_t *w, const int32_t *out_off, const int32_t *in_eid, int32_t *out_w,
                               int32_t *in_w, int32_t *out_wmin, const SolverCopy &c,
                               hipStream_t stream);
 // per-edge 4-byte values through the builder's permutation (perm[k] = COO
