@@ -217,7 +217,7 @@ typedef struct {
 typedef enum {
   SSSP_KERNEL_PERSISTENT = 0, /* rounds_kernel: cooperative grid, grid barriers */
   SSSP_KERNEL_WORKGROUP = 1,  /* wg_rounds_kernel: one workgroup per solve */
-  SSSP_KERNEL_SMALL = 2       /* small_rounds_kernel: one workgroup, state in LDS */
+  SSSP_KERNEL_SMALL = 2       /* small_rounds_kernel: one workgroup per solve, state in LDS */
 } sssp_kernel;
 
 typedef struct {
@@ -407,10 +407,10 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
  *                with block barriers only (default 8192; negative: never);
  *   block_units: otherwise the phase runs on about (work units) /
  *                block_units blocks, a power of two (default 2048);
- *   small_n:     a single solve (sssp_solve, sssp_solve_target, the
- *                sequence plan) of a graph with at most this many vertices
- *                runs all its rounds in one workgroup with the per-vertex
- *                state in LDS (default and maximum 4096; negative: never);
+ *   small_n:     a solve whose graph, or a batch whose graphs all, have at
+ *                most this many vertices runs all rounds of each instance in
+ *                a workgroup of its own with the per-vertex state in LDS
+ *                (default and maximum 4096; negative: never);
  *   wg:          solves whose graphs all run C scope OPEN run each instance
  *                in a workgroup of its own, with block barriers only (up to
  *                `blocks` workgroups at a time), and so does the tree pass

@@ -598,9 +598,7 @@ __global__ __launch_bounds__(256) void wmin_short_kernel(const int32_t *out_off,
     const int32_t e = out_off[v + 1];
     for (int32_t k = out_off[v] + l; k < e; k += kShortLanes) mn = kmin(mn, out_w[k]);
   }
-  mn = kmin(mn, dpp_mov<kDppQuadSwap1>(mn));
-  mn = kmin(mn, dpp_mov<kDppQuadSwap2>(mn));
-  mn = kmin(mn, dpp_mov<kDppHalfMirror>(mn));
+  mn = lanes8_min(mn);
   if (v < n && l == 0) out_wmin[v] = mn;
 }
 

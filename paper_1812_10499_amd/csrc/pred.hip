@@ -13,6 +13,8 @@
 // level 0 holds the source and every vertex with a strict tight in-edge, a
 // queued y gets level(y) = 1 + min level over equal-cost tight tails, and
 // pred[y] = the smallest such edge id with level(v) = level(y) - 1.
+#include <atomic>
+
 #include "sssp_dev.h"
 #include "sssp_kernels.h"
 
@@ -193,6 +195,23 @@ hipError_t fault_flag_take(int32_t *out, hipStream_t stream) {
     if ((e = hipMemcpyToSymbol(HIP_SYMBOL(g_fault_flag), &zero, sizeof(zero))) != hipSuccess)
       return e;
   }
+  return hipSuccess;
+}
+
+hipError_t fault_flag_address(int32_t **out) {
+  static std::atomic<int32_t *> known[64];
+  int dev = 0;
+  hipError_t e;
+  if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  int32_t *p = known[dev].load();
+  if (!p) {
+    void *q = nullptr;
+    if ((e = hipGetSymbolAddress(&q, HIP_SYMBOL(g_fault_flag))) != hipSuccess) return e;
+    p = (int32_t *)q;
+    known[dev].store(p);
+  }
+  *out = p;
   return hipSuccess;
 }
 

@@ -1,250 +1,423 @@
-// The rounds of a single solve on a small graph (n <= kSmallN) in one
-// workgroup, with the whole per-vertex state in LDS: the (D, parent) keys,
-// both C buffers, the relax set, the open lists and the last-relaxed D of
-// label-correcting relax.  Only the graph arrays are read from global memory
-// (through this CU's L2).  The phases are separated by block barriers alone,
-// so a round costs a few microseconds instead of the grid barriers and
-// hand-overs of the persistent kernel; results and counters are the same
-// round for round (Section VI's rounds in the adopted order: relax, minD and
-// the threshold, the lower bounds of Eq. 1, fix).  The keys are written back
-// to global memory at the end for the emit pass.
+// The rounds of solves on small graphs (n <= kSmallN), each in one workgroup
+// with the whole per-vertex state in LDS: the (D, parent) keys, both C
+// buffers, the relax set, the D of each vertex's last relax and the
+// out-offsets.  Only the edges are read from global memory (through this CU's
+// L2), and of a vertex's in-edges the kRegEdges lightest stay in registers.
+// Instance i of a batch runs on block i.  Results and counters are those of
+// the persistent kernel, round for round (Section VI's rounds in the adopted
+// order: relax, minD and the threshold, the lower bounds of Eq. 1, fix).  The
+// block writes the costs and parents itself, so a solve is one launch.
+//
+// What bounds it: latency.  A round is three block barriers, one global read
+// per relaxed edge, an LDS atomic, two block minima and the in-edges' LDS
+// gathers; a solve has tens of rounds.  1003 vertices of degree 8: 17 rounds,
+// 80 -> 48 us against a block scan and a window search per relax, separate
+// bound and fix passes, one register edge, a launch of its own for the costs;
+// 4096 vertices: 21 rounds, 205 -> 140 us.  A batch of 64 solves on 4001
+// vertices takes 154 us here and 1.6 ms on the persistent kernel, whose every
+// round waits for all the instances.
 #include "sssp_dev.h"
 #include "sssp_kernels.h"
 
 namespace sssp {
 
-constexpr int SBS = 1024;  // threads of the workgroup
-static_assert(SBS == 1024, "the relax window search covers 1024 items");
-constexpr int kSlots = kSmallN / SBS;     // vertices per thread: y = tid + k * SBS
-static_assert(kSlots * SBS == kSmallN, "whole slots");
+constexpr int kRegEdges = 4;   // a vertex's lightest in-edges kept in registers
+constexpr int kItemLanes = 8;  // lanes that share a relax item's out-list
+constexpr int32_t kLongOut = 64;  // longer out-lists are relaxed by the whole block
 
 // The open set O is implicit: y is open iff it is discovered (D < INF) and
-// not fixed (C < INF; fixed vertices carry C = INF in both buffers, and a
-// discovered vertex never has C = INF otherwise, as C <= D).
+// not fixed (C < INF; fixed vertices carry C = INF, and a discovered vertex
+// never has C = INF otherwise, as C <= D).
+template <int N, int NW>
 struct SmallLds {
-  unsigned long long D[kSmallN];  // (D << 32) | equal-cost flag << 31 | edge id
-  int32_t C[2][kSmallN];          // lower bounds by round parity (INF: fixed)
-  int32_t F[kSmallN];             // relax set: vertex ...
-  int32_t FD[kSmallN];            // ... and the D it is relaxed with
-  int32_t DR[kSmallN];            // label-correcting: D of the last relax (INF: never)
-  int32_t pfx[SBS + 1];           // out-degree prefix of a window of relax items
-  int32_t wbase[SBS];             // out-list start of a window item
-  int32_t wdx[SBS];               // its relax D
-  uint64_t scan[SBS / SSSP_WAVE + 1];
-  int32_t red[2 * (SBS / SSSP_WAVE)];
-  int32_t nF, nF2, nO, target_hit;
+  unsigned long long D[N];  // (D << 32) | equal-cost flag << 31 | edge id
+  int32_t C[2][N];          // lower bounds by round parity (INF: fixed)
+  int32_t DR[N];            // D of the last relax, or of the coming one (INF: never)
+  int32_t off[N + 1];       // out-offsets
+  uint16_t F[N];            // relax set
+  uint16_t L[N];            // its members with long out-lists
+  int32_t red[2][2 * NW];   // by round parity
+  int32_t nF, nL, target_hit, ndegen;
   unsigned long long relaxed, scanned, visits, settled;
 };
 
-// m_y of Eq. 1 over y's weight-ordered in-list (first edge from registers):
-// the scan stops at the first edge with minD + w >= lim, as every later term
-// max(C[v], minD) + w is at least minD + w.
+// Levels of float32 equal-cost vertices (the rule at the emit pass): the
+// block's queue q[0, nd) of caller ids, all of one instance whose costs and
+// parents (-2: queued) start at D and pred.
 template <class V>
-__device__ __forceinline__ int32_t small_m(const GraphDev &G, const int32_t *Cold, int32_t b,
-                                           int32_t deg, int32_t s0, int32_t w0, int32_t md,
-                                           int32_t lim) {
-  int32_t m = V::INF;
-  if (deg == 0 || V::add(md, w0) >= lim) return m;
-  {
-    const int32_t cv = Cold[s0];
-    if (cv != V::INF) m = V::add(kmax(cv, md), w0);
+__device__ int small_degen(const GraphDev &G, const int32_t *D, int32_t *pred, const int32_t *q,
+                           int nd, int32_t *lvl, int32_t *flag) {
+  int bad = 0;
+  for (int lv = 0;; ++lv) {
+    for (int i = threadIdx.x; i < nd; i += blockDim.x) {
+      flag[i] = 0;
+      const int32_t y = q[i];
+      if (lvl[y] != -1) continue;
+      const int32_t dy = D[y];
+      for (int32_t j = G.u_in_off[y]; j < G.u_in_off[y + 1]; ++j) {
+        const int32_t v = G.u_in_src[j], dv = D[v];
+        if (dv == dy && V::add(dv, G.u_in_w[j]) == dy &&
+            (pred[v] == -2 ? lvl[v] : 0) == lv) {
+          flag[i] = 1;
+          break;
+        }
+      }
+    }
+    __syncthreads();
+    int changed = 0;
+    for (int i = threadIdx.x; i < nd; i += blockDim.x) {
+      if (flag[i]) {
+        lvl[q[i]] = lv + 1;
+        changed = 1;
+      }
+    }
+    if (!__syncthreads_or(changed)) break;
   }
-  for (int32_t j = 1; j < deg; ++j) {
-    const int2 e = G.in_sw[b + j];  // tail, weight
-    const int32_t w = e.y;
-    if (V::add(md, w) >= kmin(lim, m)) break;
-    const int32_t cv = Cold[e.x];
-    if (cv != V::INF) m = kmin(m, V::add(kmax(cv, md), w));
+  for (int i = threadIdx.x; i < nd; i += blockDim.x) {
+    const int32_t y = q[i], dy = D[y], ly = lvl[y];
+    int32_t best = -1;
+    if (ly >= 1) {
+      for (int32_t j = G.u_in_off[y]; j < G.u_in_off[y + 1]; ++j) {
+        const int32_t v = G.u_in_src[j], dv = D[v];
+        if (dv == dy && V::add(dv, G.u_in_w[j]) == dy &&
+            (pred[v] == -2 ? lvl[v] : 0) == ly - 1) {
+          best = G.u_in_eid[j];
+          break;
+        }
+      }
+    }
+    flag[i] = best;
   }
-  return m;
+  __syncthreads();
+  for (int i = threadIdx.x; i < nd; i += blockDim.x) {
+    pred[q[i]] = flag[i];
+    if (flag[i] < 0) bad = 1;
+  }
+  return __syncthreads_or(bad);
 }
 
-template <class V>
-__global__ __launch_bounds__(SBS) void small_rounds_kernel(RoundArgs a) {
-  __shared__ SmallLds s;
+// T threads, each owning the vertices tid + k * T, k < SLOTS.  pred nullable;
+// fault: the device's fault flag.
+template <class V, bool BATCH, int T, int SLOTS>
+__global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *pred,
+                                                         int32_t *fault) {
+  constexpr int N = T * SLOTS, NW = T / SSSP_WAVE;
+  static_assert(N <= 65536, "vertex ids fit 16 bits");
+  __shared__ SmallLds<N, NW> s;
   const int tid = threadIdx.x;
-  const GraphDev &G = a.g;
+  int32_t sb = 0, gi = 0, usrc = a.source;
+  if constexpr (BATCH) {
+    const InstDev id = a.insts[blockIdx.x];
+    sb = id.sbase;
+    gi = id.graph;
+    usrc = id.source;
+  }
+  const GraphDev G = graph_of<BATCH>(a, gi);  // by value: its fields stay in registers
   const int n = G.n;
-  const bool lc = G.lc != 0, all = a.scope_all != 0;
-  Ctl *ctl = a.ctl;
-  int32_t src = a.source, tgt = a.target;
+  const bool lc = G.lc != 0, all = G.all != 0;
+  int32_t src = usrc, tgt = BATCH ? -1 : a.target;
   if (G.rank) {
     src = G.rank[src];
     if (tgt >= 0) tgt = G.rank[tgt];
   }
-  // this thread's vertices: in-list offset and length, lightest in-edge, out_wmin
-  int32_t ib[kSlots], id[kSlots], s0[kSlots], w0[kSlots], owm[kSlots];
+  // this thread's vertices: in-degree, in-list offset, out_wmin, the lightest
+  // in-edges (INF weights past the list's end)
+  int32_t id[SLOTS], ib[SLOTS], owm[SLOTS];
+  uint32_t es[SLOTS][(kRegEdges + 1) / 2];  // tails, two to a word
+  int32_t ew[SLOTS][kRegEdges];
 #pragma unroll
-  for (int k = 0; k < kSlots; ++k) {
-    const int y = tid + k * SBS;
-    ib[k] = id[k] = s0[k] = 0;
-    w0[k] = owm[k] = V::INF;
+  for (int k = 0; k < SLOTS; ++k) {
+    const int y = tid + k * T;
+    id[k] = ib[k] = 0;
+    owm[k] = V::INF;
     if (y < n) {
-      const int4 rec = G.vrec[2 * y];  // out_off, out_degree, in_off, in_degree
-      ib[k] = rec.z;
-      id[k] = rec.w;
-      owm[k] = G.vrec[2 * y + 1].x;
-      if (rec.w > 0) {
-        s0[k] = G.in_src[rec.z];
-        w0[k] = G.in_w[rec.z];
-      }
+      const int4 rec = G.vin[y];  // in_off, in_degree, the lightest in-edge's tail and weight
+      ib[k] = rec.x;
+      id[k] = rec.y;
+      owm[k] = G.out_wmin[y];
+      s.off[y] = G.out_off[y];
       const bool is_s = y == src;
       s.D[y] = make_key(is_s ? 0 : V::INF, -1, false);
       s.C[0][y] = s.C[1][y] = is_s ? V::INF : 0;  // the source is fixed from the start
-      s.DR[y] = V::INF;
+      s.DR[y] = is_s ? 0 : V::INF;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < SLOTS; ++k) {
+#pragma unroll
+    for (int q = 0; q < kRegEdges; ++q) {
+      ew[k][q] = V::INF;
+      if (q % 2 == 0) es[k][q / 2] = 0u;
+      if (q < id[k]) {
+        const int2 e = G.in_sw[ib[k] + q];
+        es[k][q / 2] |= (uint32_t)e.x << (16 * (q % 2));
+        ew[k][q] = e.y;
+      }
     }
   }
   if (tid == 0) {
-    s.F[0] = src;
-    s.FD[0] = 0;
+    s.off[n] = G.out_off[n];
+    s.F[0] = (uint16_t)src;
     s.nF = 1;
-    s.nO = 0;
+    s.nL = 0;
+    s.ndegen = 0;
     s.target_hit = (tgt >= 0 && tgt == src) ? 1 : 0;
     s.relaxed = s.scanned = s.visits = 0ull;
     s.settled = 1ull;  // the source
   }
+  // per-thread counts, summed at the end
+  unsigned long long nrel = 0, nscan = 0;
+  uint32_t nfix = 0, nvis = 0;
   __syncthreads();
   int r = 0, status = 0;
   for (;;) {
     if (tgt >= 0 && s.target_hit) break;  // the frontier that fixed it is not relaxed
     ++r;
-    if (r > a.max_rounds) {
+    if (r > n + 1 || r > a.max_rounds) {
       status = 7;
       break;
     }
     const int cur = r & 1;  // the bound step reads C[cur] and writes C[cur ^ 1]
-    // (A) relax the relax set's out-edges, each from its D at the start of
-    // the step (first discoveries join O by getting a finite D)
+    // (A) relax the relax set's out-edges, each vertex from the D it had when
+    // it joined the set (first discoveries join O by getting a finite D):
+    // kItemLanes lanes to an item, two items at a time
     const int nF = s.nF;
-    unsigned long long nrel = 0;
-    for (int i0 = 0; i0 < nF; i0 += SBS) {
-      const int i = i0 + tid;
-      int32_t deg = 0;
-      if (i < nF) {
-        const int32_t x = s.F[i];
-        const int32_t b = G.out_off[x];
-        deg = G.out_off[x + 1] - b;
-        s.wbase[tid] = b;
-        s.wdx[tid] = s.FD[i];
-        if (lc) s.DR[x] = s.FD[i];
+    auto relax_edge = [&](int32_t dx, int32_t pos) {
+      const int4 er = G.out_rec[pos];  // head, weight, edge id, the head's out_wmin
+      const int32_t cand = V::add(dx, er.y);
+      atomicMin(&s.D[er.x], make_key(cand, er.z, cand == dx));
+    };
+    {
+      constexpr int GR = T / kItemLanes;
+      const int g = tid / kItemLanes, l = tid % kItemLanes;
+      for (int i = g; i < nF; i += 2 * GR) {
+        int32_t b[2], e[2], dx[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int iu = i + u * GR;
+          b[u] = e[u] = dx[u] = 0;
+          if (iu < nF) {
+            const int x = s.F[iu];
+            b[u] = s.off[x];
+            e[u] = s.off[x + 1];
+            dx[u] = s.DR[x];
+            if (l == 0) {
+              nrel += (unsigned long long)(e[u] - b[u]);
+              if (e[u] - b[u] > kLongOut) s.L[atomicAdd(&s.nL, 1)] = (uint16_t)x;
+            }
+            if (e[u] - b[u] > kLongOut) e[u] = b[u];
+          }
+        }
+        for (int32_t k = l; b[0] + k < e[0] || b[1] + k < e[1]; k += kItemLanes) {
+          int4 er[2];
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            if (b[u] + k < e[u]) er[u] = G.out_rec[b[u] + k];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            if (b[u] + k < e[u]) {
+              const int32_t cand = V::add(dx[u], er[u].y);
+              atomicMin(&s.D[er[u].x], make_key(cand, er[u].z, cand == dx[u]));
+            }
+          }
+        }
       }
-      uint64_t tot;
-      s.pfx[tid] = (int32_t)block_excl_scan64<SBS>((uint64_t)deg, s.scan, &tot);
-      __syncthreads();
-      const int ET = (int)tot;
-      nrel += (unsigned long long)ET;
-      for (int e = tid; e < ET; e += SBS) {
-        // the last window item with pfx <= e (an 8-ary search: four LDS steps)
-        const int lo = search1024(s.pfx, (uint32_t)e);
-        const int32_t pos = s.wbase[lo] + (e - s.pfx[lo]);
-        const int4 er = G.out_rec[pos];  // head, weight, edge id, the head's out_wmin
-        const int32_t y = er.x;
-        const int32_t w = er.y;
-        const int32_t eid = er.z;
-        const int32_t dx = s.wdx[lo];
-        const int32_t cand = V::add(dx, w);
-        atomicMin(&s.D[y], make_key(cand, eid, cand == dx));
+    }
+    __syncthreads();
+    const int nL = s.nL;
+    if (nL > 0) {
+      for (int i = 0; i < nL; ++i) {
+        const int x = s.L[i];
+        const int32_t e = s.off[x + 1], dx = s.DR[x];
+        for (int32_t k = s.off[x] + tid; k < e; k += T) relax_edge(dx, k);
       }
       __syncthreads();
     }
+    if (tid == 0) s.nF = 0;  // (read by all before the barrier above)
     const int32_t *Cold = s.C[cur];
     int32_t *Cnew = s.C[cur ^ 1];
-    // (B) minD and the threshold over O, and |O|
+    // (B) minD and the threshold over O
     int32_t md = V::INF, th = V::INF;
-    int cnt = 0;
+    int32_t dy[SLOTS], c[SLOTS];
 #pragma unroll
-    for (int k = 0; k < kSlots; ++k) {
-      const int y = tid + k * SBS;
+    for (int k = 0; k < SLOTS; ++k) {
+      const int y = tid + k * T;
+      dy[k] = c[k] = V::INF;
       if (y < n) {
-        const int32_t dy = (int32_t)(s.D[y] >> 32);
-        if (dy != V::INF && Cold[y] != V::INF) {
-          md = kmin(md, dy);
-          th = kmin(th, V::add(dy, owm[k]));
-          ++cnt;
+        dy[k] = (int32_t)(s.D[y] >> 32);
+        c[k] = Cold[y];
+        if (dy[k] != V::INF && c[k] != V::INF) {
+          md = kmin(md, dy[k]);
+          th = kmin(th, V::add(dy[k], owm[k]));
         }
       }
     }
+    md = wave_min(md);
+    th = wave_min(th);
     {
-      const long long c = wave_sum64((long long)cnt);
-      if (lane_id() == 0 && c) atomicAdd(&s.nO, (int32_t)c);
+      int32_t *red = s.red[cur];
+      if (lane_id() == 0) {
+        red[tid / SSSP_WAVE] = md;
+        red[NW + tid / SSSP_WAVE] = th;
+      }
+      __syncthreads();
+      md = red[0];
+      th = red[NW];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) {
+        md = kmin(md, red[i]);
+        th = kmin(th, red[NW + i]);
+      }
     }
-    block_min2<SBS>(md, th, s.red);  // its barriers also publish nO
-    const int nO = s.nO;
-    if (tid == 0) s.relaxed += nrel;
-    if (nO == 0) break;  // (A) left nothing open
+    if (md == V::INF) break;  // (A) left nothing open
+    if (tid == 0) s.nL = 0;
     // (C) lower bounds (Eq. 1), Jacobi over C[cur]; SP_4's scope also
     // raises C of undiscovered vertices (an unreachable one, C = INF, keeps
-    // it).  The counters take whole in-degrees.
-    unsigned long long nscan = 0;
+    // it).  In-lists ascend by weight and every term max(C[v], minD) + w is
+    // at least minD + w, so a scan stops at the first edge with
+    // minD + w >= min(D[y], m_y) (D = INF for undiscovered ones); the slots'
+    // register edges go side by side.  The counters take whole in-degrees.
+    int32_t m[SLOTS];
+    bool on[SLOTS];
 #pragma unroll
-    for (int k = 0; k < kSlots; ++k) {
-      const int y = tid + k * SBS;
-      if (y < n) {
-        const int32_t dy = (int32_t)(s.D[y] >> 32);
-        const int32_t c = Cold[y];
-        const bool open = dy != V::INF && c != V::INF;
-        const bool undiscovered = dy == V::INF && all;
-        if (open || undiscovered) {
-          // m_y matters below min(D[y], m_y); D = INF for undiscovered ones
-          const int32_t m = c == V::INF ? V::INF
-                                        : small_m<V>(G, Cold, ib[k], id[k], s0[k], w0[k], md, dy);
-          Cnew[y] = kmax(kmax(c, md), kmin(dy, m));
-          nscan += (unsigned long long)id[k];
+    for (int k = 0; k < SLOTS; ++k) {
+      m[k] = V::INF;
+      on[k] = c[k] != V::INF && (dy[k] != V::INF || all);
+    }
+#pragma unroll
+    for (int q = 0; q < kRegEdges; ++q) {
+      int32_t cv[SLOTS];
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k) {
+        on[k] = on[k] && V::add(md, ew[k][q]) < kmin(dy[k], m[k]);
+        cv[k] = Cold[on[k] ? (es[k][q / 2] >> (16 * (q % 2))) & 0xffffu : 0u];
+      }
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k)
+        if (on[k] && cv[k] != V::INF) m[k] = kmin(m[k], V::add(kmax(cv[k], md), ew[k][q]));
+    }
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k) {
+      if (on[k] && id[k] > kRegEdges) {
+        for (int32_t j = kRegEdges; j < id[k]; ++j) {
+          const int2 e = G.in_sw[ib[k] + j];  // tail, weight
+          if (V::add(md, e.y) >= kmin(dy[k], m[k])) break;
+          const int32_t cv = Cold[e.x];
+          if (cv != V::INF) m[k] = kmin(m[k], V::add(kmax(cv, md), e.y));
         }
       }
     }
-    if (tid == 0) s.nF2 = 0;
-    __syncthreads();
-    // (D) fix: C' >= D or D <= thr.  Fixed vertices get C = INF in both
-    // buffers; the next relax set is the newly fixed vertices (label-
-    // correcting: those and the survivors whose D fell since their last
-    // relax, the fixed ones only if it fell)
-    unsigned long long nfix = 0;
+    // (These chains of global reads are the longest part of a round at 4096
+    // vertices, 2.8 of 6.7 us.  Other ways measured there, at 140 us a solve:
+    // 6 or 8 register edges 140 and 160; the slots' chains side by side 166;
+    // four edges a step 157; the lists scanned by groups of 8 lanes from an
+    // LDS queue 155.)
+    // (D) fix: C' >= D or D <= thr.  The next relax set is the newly fixed
+    // vertices (label-correcting: those and, in the first bucket above minD,
+    // the survivors whose D fell since their last relax, the fixed ones only
+    // if it fell); its places come from one LDS atomic per wave
+    uint64_t push[SLOTS];
+    int npush = 0;
 #pragma unroll
-    for (int k = 0; k < kSlots; ++k) {
-      const int y = tid + k * SBS;
+    for (int k = 0; k < SLOTS; ++k) {
+      const int y = tid + k * T;
+      const bool disc = dy[k] != V::INF, live = c[k] != V::INF;
+      const bool open = disc && live, step = open || (!disc && all);  // step (C) covers y
+      // a fixed or unreachable vertex keeps C = INF
+      const int32_t cn = live ? kmax(kmax(c[k], md), kmin(dy[k], m[k])) : V::INF;
+      const bool fix = open && (cn >= dy[k] || dy[k] <= th);
+      bool p = false;
       if (y < n) {
-        const int32_t dy = (int32_t)(s.D[y] >> 32);
-        if (dy != V::INF && Cold[y] != V::INF) {
-          const int32_t cn = Cnew[y];
-          const bool relax_again = !lc || dy < s.DR[y];
-          const bool fix = cn >= dy || dy <= th;
-          if (fix) {
-            s.C[0][y] = s.C[1][y] = V::INF;
-            ++nfix;
-            if (y == tgt) s.target_hit = 1;
-          }
-          // an open vertex only while in the first bucket above minD
-          if (relax_again && (fix || (lc && dy < V::add(md, G.delta)))) {
-            const int q = atomicAdd(&s.nF2, 1);
-            s.F[q] = y;
-            s.FD[q] = dy;
-          }
-        }
+        if (step) nscan += (unsigned long long)id[k];
+        if (step || !live) Cnew[y] = fix ? V::INF : cn;
+        nvis += open ? 1u : 0u;
+        nfix += fix ? 1u : 0u;
+        if (fix && y == tgt) s.target_hit = 1;
+        p = open && (fix || (lc && dy[k] < V::add(md, G.delta)));
+        if (lc && p) p = dy[k] < s.DR[y];
+        if (p) s.DR[y] = dy[k];
       }
+      push[k] = __ballot(p);
+      npush += __popcll(push[k]);
     }
-    const long long f = wave_sum64((long long)nfix), sc = wave_sum64((long long)nscan);
-    if (lane_id() == 0) {
-      if (f) atomicAdd(&s.settled, (unsigned long long)f);
-      if (sc) atomicAdd(&s.scanned, (unsigned long long)sc);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      s.visits += (unsigned long long)nO;
-      s.nF = s.nF2;
-      s.nO = 0;
+    if (npush) {  // (wave-uniform)
+      int at = 0;
+      if (lane_id() == 0) at = atomicAdd(&s.nF, npush);
+      at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k) {
+        const uint64_t mine = push[k];
+        if ((mine >> lane_id()) & 1ull)
+          s.F[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u))] =
+              (uint16_t)(tid + k * T);
+        at += __popcll(mine);
+      }
     }
     __syncthreads();
   }
   __syncthreads();
-  // the keys for the emit pass, and the control block it and the host read
-  for (int y = tid; y < n; y += SBS) a.D64[y] = s.D[y];
-  if (tid == 0) {
+  // costs and parents (the emit pass's rule), in the caller's numbering
+  int32_t *cost = a.D + sb, *queue = a.degen + sb, *lvl = a.lvl + sb;
+  int32_t *par = pred ? pred + sb : nullptr;
+#pragma unroll
+  for (int k = 0; k < SLOTS; ++k) {
+    const int y = tid + k * T;
+    if (y < n) {
+      const int32_t uy = G.vid ? G.vid[y] : y;
+      const unsigned long long key = s.D[y];
+      const int32_t d = (int32_t)(key >> 32);
+      cost[uy] = d;
+      if (par) {
+        int32_t p = -1;
+        if (uy != usrc && d != V::INF) {
+          if (key & kKeyEqualCost) {
+            p = -2;
+            queue[atomicAdd(&s.ndegen, 1)] = uy;
+            lvl[uy] = -1;
+          } else {
+            p = (int32_t)(key & kKeyEidMask);
+          }
+        }
+        par[uy] = p;
+      }
+    }
+  }
+  {
+    const long long v0 = wave_sum64((long long)nrel), v1 = wave_sum64((long long)nscan);
+    const long long v2 = wave_sum64((long long)nvis), v3 = wave_sum64((long long)nfix);
+    if (lane_id() == 0) {
+      if (v0) atomicAdd(&s.relaxed, (unsigned long long)v0);
+      if (v1) atomicAdd(&s.scanned, (unsigned long long)v1);
+      if (v2) atomicAdd(&s.visits, (unsigned long long)v2);
+      if (v3) atomicAdd(&s.settled, (unsigned long long)v3);
+    }
+  }
+  __syncthreads();
+  const int nd = s.ndegen;
+  if (nd > 0 && small_degen<V>(G, cost, par, queue, nd, lvl, a.flag + sb)) status = 7;
+  if (tid != 0) return;
+  if (status) atomicOr(fault, 1);
+  Ctl *ctl = a.ctl;
+  if constexpr (BATCH) {
+    const int inst = blockIdx.x;
+    a.irounds[inst] = r;
+    a.iscanned[3 * inst] = s.scanned;
+    a.iscanned[3 * inst + 1] = s.visits;
+    a.iscanned[3 * inst + 2] = s.relaxed;
+    if (a.idead) a.idead[2 * inst] = a.idead[2 * inst + 1] = 0ull;  // counted round by round
+    if (a.istat) {
+      a.istat[4 * inst] = a.istat[4 * inst + 3] = 0;
+      a.istat[4 * inst + 1] = (long long)s.settled;
+      a.istat[4 * inst + 2] = (long long)s.relaxed;
+    }
+    if (status) atomicMax(&ctl->status, status);
+  } else {
     ctl->front_ctr[0] = ctl->front_ctr[1] = 0ull;
     ctl->open_ctr[0] = ctl->open_ctr[1] = 0ull;
     ctl->live_ctr[0] = ctl->live_ctr[1] = 0ull;
     ctl->go = ctl->go_a = 0u;
-    ctl->deg_count = 0;
+    ctl->deg_count = nd;
     ctl->solo_phases = 0;
     ctl->dead_deg = ctl->dead_deg_r = 0ull;
     ctl->rounds = r;
@@ -258,27 +431,54 @@ __global__ __launch_bounds__(SBS) void small_rounds_kernel(RoundArgs a) {
   }
 }
 
-template <class V>
-static hipError_t launch_small_t(const RoundArgs &a, int32_t *pred, const KernelTimer *timer,
-                                 Launcher &L) {
-  hipError_t e;
-  if (a.total > kSmallN || a.num_inst != 1) return hipErrorInvalidValue;
-  RoundArgs arg = a;
-  void *params[] = {&arg};
-  if (L.graph) timer = nullptr;
-  if (timer && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
-  if ((e = launch_kernel(L, (const void *)small_rounds_kernel<V>, dim3(1), dim3(SBS), params,
-                         false)) != hipSuccess)
-    return e;
-  if (timer && (e = hipEventRecord(timer->stop, L.stream)) != hipSuccess) return e;
-  LaunchGeom geo = {1, 1};
-  return launch_pred(V::INF == KeyF32::INF, false, a, pred, geo, nullptr, a.total, L);
+// A batch's control block (its instances raise the status).
+__global__ void small_reset_kernel(Ctl *ctl) {
+  ctl->status = 0;
+  ctl->rounds = 0;
+  ctl->deg_count = 0;
+  ctl->solo_phases = 0;
 }
 
-hipError_t launch_small(bool f32, const RoundArgs &a, int32_t *pred, const KernelTimer *timer,
-                        Launcher &L) {
-  return f32 ? launch_small_t<KeyF32>(a, pred, timer, L)
-             : launch_small_t<KeyI32>(a, pred, timer, L);
+template <class V, bool BATCH>
+static hipError_t launch_small_t(const RoundArgs &a, int32_t *pred, int32_t max_n,
+                                 const KernelTimer *timer, Launcher &L) {
+  hipError_t e;
+  if (max_n > kSmallN || (!BATCH && a.num_inst != 1)) return hipErrorInvalidValue;
+  RoundArgs arg = a;
+  int32_t *p = pred, *fault = nullptr;
+  if ((e = fault_flag_address(&fault)) != hipSuccess) return e;
+  Ctl *ctl = a.ctl;
+  void *params[] = {&arg, &p, &fault};
+  void *reset[] = {&ctl};
+  if (BATCH && (e = launch_kernel(L, (const void *)small_reset_kernel, dim3(1), dim3(1), reset,
+                                  false)) != hipSuccess)
+    return e;
+  if (L.graph) timer = nullptr;
+  if (timer && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
+  const dim3 grid(BATCH ? (unsigned)a.num_inst : 1u);
+  // 1024 threads also where 256 or 512 would own several vertices each:
+  // 1003 vertices take 48 us, against 58 (512 x 2) and 91 (256 x 4)
+  if (max_n <= 1024)
+    e = launch_kernel(L, (const void *)small_rounds_kernel<V, BATCH, 1024, 1>, grid, dim3(1024),
+                      params, false);
+  else if (max_n <= 2048)
+    e = launch_kernel(L, (const void *)small_rounds_kernel<V, BATCH, 1024, 2>, grid, dim3(1024),
+                      params, false);
+  else
+    e = launch_kernel(L, (const void *)small_rounds_kernel<V, BATCH, 1024, 4>, grid, dim3(1024),
+                      params, false);
+  if (e != hipSuccess) return e;
+  if (timer && (e = hipEventRecord(timer->stop, L.stream)) != hipSuccess) return e;
+  return hipSuccess;
+}
+
+hipError_t launch_small(bool f32, bool batch, const RoundArgs &a, int32_t *pred, int32_t max_n,
+                        const KernelTimer *timer, Launcher &L) {
+  if (f32)
+    return batch ? launch_small_t<KeyF32, true>(a, pred, max_n, timer, L)
+                 : launch_small_t<KeyF32, false>(a, pred, max_n, timer, L);
+  return batch ? launch_small_t<KeyI32, true>(a, pred, max_n, timer, L)
+               : launch_small_t<KeyI32, false>(a, pred, max_n, timer, L);
 }
 
 }  // namespace sssp

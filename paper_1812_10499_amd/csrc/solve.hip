@@ -1936,7 +1936,8 @@ static hipError_t launch_solve_t(const RoundArgs &a, int32_t *pred, const Launch
                                  Launcher &L) {
   hipError_t e;
   if (geo.blocks > kMaxBlocks) return hipErrorInvalidConfiguration;
-  if (!BATCH && a.total <= geo.small_n) return launch_small(V::INF == KeyF32::INF, a, pred, timer, L);
+  if (max_n <= geo.small_n)
+    return launch_small(V::INF == KeyF32::INF, BATCH, a, pred, max_n, timer, L);
   if (geo.wg && !a.scope_all)
     return launch_wg(V::INF == KeyF32::INF, BATCH, a, pred, geo, istat, max_n, timer, L);
   RoundArgs arg = a;

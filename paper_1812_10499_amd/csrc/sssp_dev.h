@@ -113,6 +113,13 @@ __device__ __forceinline__ int32_t wave_max(int32_t v) {
   return wave_reduce32(v, [](int32_t x, int32_t y) { return kmax(x, y); });
 }
 
+// Minimum over each group of eight neighbouring lanes (whole groups active).
+__device__ __forceinline__ int32_t lanes8_min(int32_t v) {
+  v = kmin(v, dpp_mov<kDppQuadSwap1>(v));
+  v = kmin(v, dpp_mov<kDppQuadSwap2>(v));
+  return kmin(v, dpp_mov<kDppHalfMirror>(v));
+}
+
 template <int CTRL>
 __device__ __forceinline__ int64_t dpp_mov64(int64_t v) {
   const int32_t lo = dpp_mov<CTRL>((int32_t)(uint32_t)v);

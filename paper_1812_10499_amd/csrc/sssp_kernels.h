@@ -159,7 +159,7 @@ constexpr int kMarks = 12;
 struct LaunchGeom {
   int blocks;  // persistent grid size (co-resident)
   int cus;
-  int small_n = 0;  // single solves of at most this many vertices run in one workgroup
+  int small_n = 0;  // solves of at most this many vertices run in one workgroup each, state in LDS
   int wg = 0;       // every instance in a workgroup of its own (scope OPEN only)
 };
 
@@ -210,6 +210,8 @@ hipError_t launch_pred(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
 // waits for `stream`, then reads (*out: 0 or 1) and clears the device's
 // fault flag, which the emit pass sets for a solve whose status is non-zero
 hipError_t fault_flag_take(int32_t *out, hipStream_t stream);
+// the flag's address on the current device (looked up once per device)
+hipError_t fault_flag_address(int32_t **out);
 hipError_t round_kernel_occupancy(bool f32, bool batch, int *blocks_per_cu);
 
 // Bytes of the static scratch region of allocation-free solves, and its
@@ -221,9 +223,10 @@ hipError_t scratch_address(void **ptr);
 hipError_t launch_wg(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
                      const LaunchGeom &geo, long long *istat, int32_t max_n,
                      const KernelTimer *timer, Launcher &L);
-// a single solve of a.total <= kSmallN vertices in one workgroup, then the emit pass
-hipError_t launch_small(bool f32, const RoundArgs &a, int32_t *pred, const KernelTimer *timer,
-                        Launcher &L);
+// every instance (max_n <= kSmallN vertices) in a workgroup of its own with its
+// state in LDS, costs and parents included
+hipError_t launch_small(bool f32, bool batch, const RoundArgs &a, int32_t *pred, int32_t max_n,
+                        const KernelTimer *timer, Launcher &L);
 
 // ------------------------------------------------------------- builder
 struct BuildTemps {
