@@ -216,7 +216,7 @@ typedef struct {
  */
 typedef enum {
   SSSP_KERNEL_PERSISTENT = 0, /* rounds_kernel: cooperative grid, grid barriers */
-  SSSP_KERNEL_WORKGROUP = 1,  /* wg_rounds_kernel: one workgroup per solve */
+  SSSP_KERNEL_WORKGROUP = 1,  /* one workgroup, or one team of workgroups, per solve */
   SSSP_KERNEL_SMALL = 2       /* small_rounds_kernel: one workgroup per solve, state in LDS */
 } sssp_kernel;
 
@@ -416,7 +416,10 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
  *                `blocks` workgroups at a time), and so does the tree pass
  *                of sssp_backward: 0 (default) when every graph has low
  *                degree spread (deg_max * n < 3m: many small rounds, deep
- *                trees), 1 always, negative never.
+ *                trees), 1 always, negative never.  By default, few
+ *                instances (at most half as many as compute units) run each
+ *                in a team of cooperating workgroups instead; one whose open
+ *                set outgrows its team runs again in one workgroup.
  */
 typedef struct {
   int32_t blocks;

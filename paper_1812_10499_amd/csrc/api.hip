@@ -181,7 +181,7 @@ sssp_status resolve_launch(DevWS &w, bool f32, bool batch, const sssp_launch *L,
   geo->small_n = kSmallN;
   if (L && L->small_n) geo->small_n = L->small_n < 0 ? 0 : (L->small_n < kSmallN ? L->small_n : kSmallN);
   const int wg = L ? L->wg : 0;
-  geo->wg = wg > 0 || (wg == 0 && low_spread) ? 1 : 0;
+  geo->wg = wg > 0 ? 1 : (wg == 0 && low_spread ? 2 : 0);
   return SSSP_OK;
 }
 
@@ -1152,7 +1152,7 @@ static sssp_status plan_record(sssp_plan_s *p, const sssp_launch *L) {
       p->seq[i].solo_edges = probe.solo_edges;
       p->seq[i].block_units = probe.block_units;
       LaunchGeom gi = geo;
-      gi.wg = wg > 0 || (wg == 0 && p->seq_low[i]) ? 1 : 0;
+      gi.wg = wg > 0 ? 1 : (wg == 0 && p->seq_low[i] ? 2 : 0);
       HIPCHK(launch_solve(p->f32, false, p->seq[i], p->seq_pred[i], gi, nullptr, p->seq_n[i],
                           nullptr, rec));
     }

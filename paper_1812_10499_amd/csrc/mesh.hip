@@ -1,0 +1,626 @@
+// The rounds of solves on graphs of low degree spread (meshes, grids) under C
+// scope OPEN, each by a team of W single-wave workgroups.  Such a solve has
+// thousands of rounds of a few hundred relaxed vertices and a few thousand
+// open ones: one workgroup is bound by its compute unit's memory pipeline
+// (13 of 18 us a round on a 1024 x 1024 grid), the grid-wide kernel by its
+// barriers and list windows.  Here a round takes 4.8 us: the chain of atomic,
+// mailbox, word, D, vertex record, in-edges and C, each through the L2 or the
+// Infinity Cache, one after another in some wave of every round (relax 2.5,
+// waiting for the words 2.8, D and C 1.5, newcomers 2.3, fix 2.1, last wait
+// 0.7 thousand cycles).  1024 x 1024 grid 80 -> 22.4 ms, 2048 x 2048 372 ->
+// 78, 64 solves of a 512 x 512 grid 9.7 -> 7.5.
+//
+// Every vertex belongs to one wave of the team (a hash of its id).  An open
+// vertex lives in a seat in its wave's registers from its discovery to its
+// fix, with its lower bound, offsets and lightest in-edges, so a round reads
+// only D and the tails' C for it.  What the waves share goes through
+// agent-scope relaxed atomics and nothing else (D, C, the mailboxes, the
+// words below), so no cache is written back or invalidated, wherever the
+// waves run; the blocks are numbered so that a team shares an XCD's L2.
+//
+// A round of wave w:
+//   relax the edges of its relax set; a first discovery goes to the owner's
+//     mailbox for (w, owner), tagged with the round;
+//   wait for its own stores, then publish (round, its minD and thr offers);
+//   read all waves' words until all carry the round: the barrier, minD and
+//     thr in one read (mailboxes are complete, and so is every D);
+//   read D and the tails' C for the open seats and the mailboxes together,
+//     seat the discoveries, publish "D read" (round);
+//   bound and fix each seat (write C, build the next relax set);
+//   read the "D read" words until all carry the round: only then may the
+//     next relax change D.  C is double-buffered by round parity, as in the
+//     other kernels, and every wave's reads of a buffer end before its next
+//     publication, so its rewriting a round later needs no barrier of its
+//     own.
+// A mailbox or a wave's seats can fill up (large open sets).  The wave says so
+// with its next word, the whole team leaves, and the one-workgroup kernel,
+// launched behind this one, runs that instance from its start; it skips the
+// others.
+#include <atomic>
+
+#include "sssp_dev.h"
+#include "sssp_kernels.h"
+
+namespace sssp {
+
+constexpr int kMeshEdges = 4;  // lightest in-edges kept with a seat
+constexpr int kBox = 16;       // mailbox entries per pair of waves and round
+constexpr int kMeshLanes = 4;  // lanes that share a relax item's out-list
+constexpr int32_t kGiveUp = 0;  // as minD: below every open vertex's D
+constexpr int32_t kReadHit = 1, kReadFull = 2;  // target fixed; seats full
+// A wait ends after this many reads (some seconds; a round takes
+// microseconds) and the solve with an internal error.
+constexpr int kSpinLimit = 1 << 24;
+
+// A store the team's other waves are to read (with agent-scope loads, which
+// pass over the L1): within one XCD it only has to reach the shared L2 (about
+// 440 cycles until done, against 830 for an agent-scope store; with the latter
+// the 1024 x 1024 grid takes 45 ms).
+__device__ __forceinline__ void put(int32_t *p, int32_t v, bool same_l2) {
+  if (same_l2) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put64(unsigned long long *p, unsigned long long v, bool same_l2) {
+  if (same_l2) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// every store of this wave has reached the point the other waves read
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ unsigned long long tagged(unsigned tag, int32_t v) {
+  return ((unsigned long long)tag << 32) | (uint32_t)v;
+}
+
+// A wave's published word: the round's low two bits (no wave is more than one
+// round ahead of another), minD's key and thr's (non-negative).
+__device__ __forceinline__ unsigned long long offers(unsigned ep, int32_t md, int32_t th) {
+  return ((unsigned long long)(ep & 3u) << 62) | ((unsigned long long)(uint32_t)md << 31) |
+         (unsigned long long)(uint32_t)th;
+}
+
+// The wave of the team that owns vertex y (W = 1 << lw): Murmur3's 32-bit
+// finalizer (Appleby), low bits.  A plain multiplicative hash sends all the
+// grid neighbours of one wave's vertices to a few waves and their mailboxes
+// fill up.
+__device__ __forceinline__ int mesh_owner(int32_t y, int lw) {
+  uint32_t h = (uint32_t)y;
+  h = (h ^ (h >> 16)) * 0x85EBCA6Bu;
+  h = (h ^ (h >> 13)) * 0xC2B2AE35u;
+  return (int)((h ^ (h >> 16)) & ((1u << lw) - 1u));
+}
+
+// Team words and mailboxes.  words: [teams][2][W]: offers, D read (round,
+// flags).  box: [parity][teams][owner][entry][sender] of (round, vertex).
+struct MeshArgs {
+  int32_t lw, teams;
+  unsigned long long *words, *box0, *box1;
+  int32_t *redo;  // per instance: the one-workgroup kernel is to run it
+};
+
+// D = INF, C = 0, the sources, empty words and mailboxes, the control block
+// and the instances' counters.  Grid y: the instance.
+template <class V, bool BATCH>
+__global__ __launch_bounds__(256) void mesh_init_kernel(RoundArgs a, MeshArgs q) {
+  const int inst = blockIdx.y;
+  int32_t sb = 0, gi = 0, src = a.source, n = a.g.n;
+  if constexpr (BATCH) {
+    const InstDev id = a.insts[inst];
+    sb = id.sbase;
+    gi = id.graph;
+    src = id.source;
+    n = id.n;
+  }
+  const GraphDev &G = graph_of<BATCH>(a, gi);
+  if (G.rank) src = G.rank[src];
+  const int t0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (int64_t y = t0; y < n; y += step) {
+    const bool is_s = y == src;
+    a.D64[sb + y] = make_key(is_s ? 0 : V::INF, -1, false);
+    a.C0[sb + y] = a.C1[sb + y] = is_s ? V::INF : 0;  // the source is fixed from the start
+  }
+  if (t0 == 0) {
+    q.redo[inst] = 0;
+    if constexpr (BATCH) {
+      a.irounds[inst] = 0;
+      for (int k = 0; k < 3; ++k) a.iscanned[3 * inst + k] = 0ull;
+      if (a.istat)
+        for (int k = 0; k < 4; ++k) a.istat[4 * inst + k] = 0;
+    }
+  }
+  if (inst != 0) return;
+  const int64_t W = (int64_t)1 << q.lw, words = 2 * W * q.teams, box = W * W * kBox * q.teams;
+  for (int64_t i = t0; i < words; i += step) q.words[i] = 0ull;
+  for (int64_t i = t0; i < box; i += step) q.box0[i] = q.box1[i] = 0ull;
+  if (t0 == 0) {
+    Ctl *c = a.ctl;
+    c->front_ctr[0] = c->front_ctr[1] = 0ull;
+    c->open_ctr[0] = c->open_ctr[1] = 0ull;
+    c->live_ctr[0] = c->live_ctr[1] = 0ull;
+    c->go = c->go_a = 0u;
+    c->deg_count = 0;
+    c->solo_phases = 0;
+    c->dead_deg = c->dead_deg_r = 0ull;
+    c->status = 0;
+    c->rounds = 0;
+    c->settled = c->relaxed = c->scanned = c->open_visits = 0;
+    c->target_id = -1;
+    c->target_hit = 0;
+  }
+}
+
+template <int kSeatMax>
+struct MeshLds {
+  int4 rel[kSeatMax];  // relax set: vertex, D to relax from, out-offset, out-degree
+  int32_t msg[kSeatMax];
+  int32_t sent[SSSP_WAVE];  // mailbox entries written this round, by owner
+};
+
+// kSeats: open vertices per lane.
+template <class V, bool BATCH, int kSeats>
+__global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, MeshArgs q) {
+  constexpr int kSeatMax = SSSP_WAVE * kSeats;
+  __shared__ MeshLds<kSeatMax> s;
+  const int l = lane_id(), lw = q.lw, W = 1 << lw;
+  // team t runs on the blocks of one residue mod 8: blocks go round-robin to
+  // the XCDs
+  const int tb = blockIdx.x >> 3, team = (tb >> lw) * 8 + (int)(blockIdx.x & 7u);
+  const int w = tb & (W - 1);
+  if (team >= q.teams) return;
+  unsigned long long *pub = q.words + (size_t)team * 2 * W, *read_d = pub + W;
+  const size_t box_team = (size_t)W * W * kBox * team;
+  unsigned long long *const box0 = q.box0 + box_team, *const box1 = q.box1 + box_team;
+  const int lp = l < W ? l : 0;  // the wave whose words this lane reads
+  unsigned ep = 1;               // rounds over all of the team's instances: the tag
+  bool lost = false;
+  // the published words of this round
+  auto await_offers = [&]() -> unsigned long long {
+    unsigned long long x = 0;
+    int spins = 0;
+    do {
+      x = ld_relaxed64(&pub[lp]);
+      lost = ++spins > kSpinLimit;
+    } while (!lost && __ballot((unsigned)(x >> 62) != (ep & 3u)));
+    asm volatile("" ::: "memory");  // nothing below is read before the words
+    return x;
+  };
+  // all "D read" words of this round: the union of their flags
+  auto await_read = [&]() -> int32_t {
+    unsigned long long x = 0;
+    int spins = 0;
+    do {
+      x = ld_relaxed64(&read_d[lp]);
+      lost = ++spins > kSpinLimit;
+    } while (!lost && __ballot((int)((unsigned)(x >> 32) - ep) < 0));
+    asm volatile("" ::: "memory");
+    int32_t f = 0;
+    if (__ballot((uint32_t)x & (uint32_t)kReadHit)) f |= kReadHit;
+    if (__ballot((uint32_t)x & (uint32_t)kReadFull)) f |= kReadFull;
+    return f;
+  };
+  // round 1 of the words: whether the team shares an XCD, and so an L2
+  bool same = false;
+  {
+    const int32_t xcc = (int32_t)(__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xffu);
+    if (l == 0) put64(&pub[w], offers(ep, xcc + 1, 0), false);
+    const unsigned long long x = await_offers();
+    same = __ballot((int32_t)((x >> 31) & 0x7fffffffu) != xcc + 1) == 0ull;
+    if (l == 0) put64(&read_d[w], tagged(ep, 0), false);
+    await_read();
+    if (lost) {
+      if (l == 0) atomicMax(&a.ctl->status, 7);
+      return;
+    }
+  }
+  for (int inst = team; inst < a.num_inst; inst += q.teams) {
+    int32_t sb = 0, gi = 0, src = a.source, n = a.g.n;
+    if constexpr (BATCH) {
+      const InstDev id = a.insts[inst];
+      sb = id.sbase;
+      gi = id.graph;
+      src = id.source;
+      n = id.n;
+    }
+    const GraphDev G = graph_of<BATCH>(a, gi);
+    const bool lc = G.lc != 0;
+    int32_t tgt = BATCH ? -1 : a.target;
+    if (G.rank) {
+      src = G.rank[src];
+      if (tgt >= 0) tgt = G.rank[tgt];
+    }
+    unsigned long long *D = a.D64 + sb;
+    int32_t *C[2] = {a.C0 + sb, a.C1 + sb};
+    // the seats: vertex (-1: free), C, D of the last relax, out_wmin, offsets
+    // and degrees, the lightest in-edges
+    int32_t y[kSeats], cy[kSeats], dr[kSeats], owm[kSeats], ioff[kSeats], ideg[kSeats];
+    int32_t ooff[kSeats], odeg[kSeats], et[kSeats][kMeshEdges], ew[kSeats][kMeshEdges];
+#pragma unroll
+    for (int u = 0; u < kSeats; ++u) {
+      y[u] = -1;
+      cy[u] = dr[u] = owm[u] = ioff[u] = ideg[u] = ooff[u] = odeg[u] = 0;
+#pragma unroll
+      for (int e = 0; e < kMeshEdges; ++e) et[u][e] = ew[u][e] = 0;
+    }
+    int nF = 0;
+    if (w == 0) {
+      const int32_t o0 = G.out_off[src];
+      if (l == 0) s.rel[0] = make_int4(src, 0, o0, G.out_off[src + 1] - o0);
+      nF = 1;
+    }
+    __syncthreads();
+    // this lane's counts, and its survivors' offers to minD and thr
+    unsigned long long nrel = 0, nscan = 0;
+    uint32_t nvis = 0, nfix = 0;
+    int32_t smd = V::INF, sth = V::INF;
+    bool full = false, gave_up = false, hit = tgt >= 0 && tgt == src;
+    int r = 0, status = 0;
+    // the first edge of this lane's first relax item, read ahead
+    int4 er = make_int4(0, 0, 0, 0);
+    bool ahead = false;
+    for (;;) {
+      if (hit) break;  // the frontier that fixed the target is not relaxed
+      ++r;
+      ++ep;
+      if (r > n + 1 || r > a.max_rounds) {  // (every wave alike)
+        status = 7;
+        break;
+      }
+      const int cur = r & 1;  // the bound step reads C[cur] and writes C[cur ^ 1]
+      int32_t *Cold = C[cur], *Cnew = C[cur ^ 1];
+      unsigned long long *box = cur ? box1 : box0;
+      // (A) relax, each item from its D at the start of the step (bit 31: an
+      // open vertex, label-correcting; INF: already relaxed at this D)
+      int32_t md = smd, th = sth;
+      if (nF) {
+        s.sent[l] = 0;
+        __syncthreads();
+        for (int i0 = 0; i0 < nF; i0 += SSSP_WAVE / kMeshLanes) {
+          const int i = i0 + l / kMeshLanes, e0 = l % kMeshLanes;
+          int4 f = make_int4(0, V::INF, 0, 0);
+          if (i < nF) f = s.rel[i];
+          const int32_t dx = f.y & 0x7fffffff;
+          const int32_t deg = i < nF && dx != V::INF ? f.w : 0;
+          if (e0 == 0) nrel += (unsigned long long)deg;
+          for (int32_t k = e0; k < deg; k += kMeshLanes) {
+            // head, weight, edge id, the head's out_wmin
+            if (i0 > 0 || k != e0 || !ahead) er = G.out_rec[f.z + k];
+            const int32_t cand = V::add(dx, er.y);
+            const unsigned long long old =
+                atomicMin(&D[er.x], make_key(cand, er.z, cand == dx));
+            const int32_t od = (int32_t)(old >> 32);
+            if (cand < od) {  // D fell: offer it to minD and thr
+              md = kmin(md, cand);
+              th = kmin(th, V::add(cand, er.w));
+            }
+            if (od == V::INF) {  // a first discovery
+              const int o = mesh_owner(er.x, lw);
+              const int p = atomicAdd(&s.sent[o], 1);
+              if (p < kBox) put64(&box[((size_t)o * kBox + p) * W + w], tagged(ep, er.x), same);
+              else full = true;
+            }
+          }
+        }
+      }
+      md = __ballot(full) ? kGiveUp : wave_min(md);
+      th = wave_min(th);
+      stores_done();
+      if (l == 0) put64(&pub[w], offers(ep, md, th), same);
+      {
+        const unsigned long long x = await_offers();
+        md = wave_min((int32_t)((x >> 31) & 0x7fffffffu));
+        th = wave_min((int32_t)(x & 0x7fffffffu));
+      }
+      if (lost) break;
+      if (md == kGiveUp || md == V::INF) {  // (every wave alike)
+        gave_up = md == kGiveUp;
+        // the words are rewritten by the team's next instance: only after
+        // every wave has read them
+        if (l == 0) put64(&read_d[w], tagged(ep, 0), same);
+        await_read();
+        break;
+      }
+      // (B) done: md and th are minD and the threshold.  D and the tails' C
+      // of the open seats, and the first two entries of every mailbox
+      unsigned long long dk[kSeats], m0, m1;
+      int32_t cv[kSeats][kMeshEdges];
+      {
+        const size_t at = (size_t)w * kBox * W + lp;
+        m0 = ld_relaxed64(&box[at]);
+        m1 = ld_relaxed64(&box[at + W]);
+      }
+#pragma unroll
+      for (int u = 0; u < kSeats; ++u) {
+        dk[u] = 0;
+#pragma unroll
+        for (int e = 0; e < kMeshEdges; ++e) cv[u][e] = V::INF;
+        if (__ballot(y[u] >= 0)) {
+          dk[u] = ld_relaxed64(&D[y[u] >= 0 ? y[u] : 0]);
+#pragma unroll
+          for (int e = 0; e < kMeshEdges; ++e) cv[u][e] = ld_relaxed(&Cold[et[u][e]]);
+        }
+      }
+      // the discoveries, gathered in LDS
+      int nmsg = 0;
+      {
+        bool v0 = l < W && (unsigned)(m0 >> 32) == ep, v1 = l < W && (unsigned)(m1 >> 32) == ep;
+        const uint64_t b0 = __ballot(v0), b1 = __ballot(v1);
+        const uint64_t lt = (1ull << l) - 1ull;
+        if (v0) s.msg[__popcll(b0 & lt)] = (int32_t)(uint32_t)m0;
+        nmsg = __popcll(b0);
+        if (v1) s.msg[nmsg + __popcll(b1 & lt)] = (int32_t)(uint32_t)m1;
+        nmsg += __popcll(b1);
+        for (int k = 2; k < kBox && __ballot(v1); ++k) {
+          const unsigned long long m = ld_relaxed64(&box[((size_t)w * kBox + k) * W + lp]);
+          v1 = v1 && (unsigned)(m >> 32) == ep;
+          const uint64_t b = __ballot(v1);
+          const int p = nmsg + __popcll(b & lt);
+          if (v1 && p < kSeatMax) s.msg[p] = (int32_t)(uint32_t)m;
+          nmsg += __popcll(b);
+        }
+      }
+      bool fresh[kSeats];
+      {
+        __syncthreads();
+        int taken = 0;
+#pragma unroll
+        for (int u = 0; u < kSeats; ++u) {
+          fresh[u] = false;
+          const uint64_t fm = __ballot(y[u] < 0);
+          if (taken < nmsg && fm) {  // (wave-uniform)
+            const int p = taken + __popcll(fm & ((1ull << l) - 1ull));
+            fresh[u] = y[u] < 0 && p < nmsg && p < kSeatMax;
+            if (fresh[u]) {
+              y[u] = s.msg[p];
+              dk[u] = ld_relaxed64(&D[y[u]]);
+              const int4 ra = G.vrec[2 * y[u]], rb = G.vrec[2 * y[u] + 1];
+              ooff[u] = ra.x;
+              odeg[u] = ra.y;
+              ioff[u] = ra.z;
+              ideg[u] = ra.w;
+              owm[u] = rb.x;
+              et[u][0] = rb.y;
+              ew[u][0] = ra.w > 0 ? rb.z : V::INF;
+              cy[u] = 0;       // C of an undiscovered vertex
+              dr[u] = V::INF;  // never relaxed
+            }
+            taken += __popcll(fm);
+          }
+        }
+        full = taken < nmsg;
+      }
+      // the rest of the newcomers' lightest in-edges, then their tails' C
+#pragma unroll
+      for (int u = 0; u < kSeats; ++u) {
+        if (fresh[u]) {
+#pragma unroll
+          for (int e = 1; e < kMeshEdges; ++e) {
+            const int2 x = e < ideg[u] ? G.in_sw[ioff[u] + e] : make_int2(0, V::INF);
+            et[u][e] = x.x;
+            ew[u][e] = x.y;
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kSeats; ++u) {
+        if (fresh[u]) {
+#pragma unroll
+          for (int e = 0; e < kMeshEdges; ++e) cv[u][e] = ld_relaxed(&Cold[et[u][e]]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kSeats; ++u) asm volatile("" : "+v"(dk[u]));  // every D has arrived
+      if (tgt < 0 && l == 0) put64(&read_d[w], tagged(ep, full ? kReadFull : 0), same);
+      // vertices fixed last round: C = INF in this round's buffer too
+      for (int i = l; i < nF; i += SSSP_WAVE) {
+        const int4 f = s.rel[i];
+        if (f.y >= 0) put(&Cnew[f.x], V::INF, same);
+      }
+      __syncthreads();
+      // (C) lower bounds (Eq. 1), Jacobi, and (D) fix, seat by seat.  An
+      // in-edge with minD + w >= D[y] cannot lower C'[y]; in-lists ascend by
+      // weight.
+      smd = sth = V::INF;
+      nF = 0;
+      bool hit_now = false;
+#pragma unroll
+      for (int u = 0; u < kSeats; ++u) {
+        if (!__ballot(y[u] >= 0)) continue;
+        bool push = false;
+        int32_t fd = 0;
+        const int32_t x = y[u];
+        if (x >= 0) {
+          const int32_t dy = (int32_t)(dk[u] >> 32);
+          int32_t m = V::INF;
+#pragma unroll
+          for (int e = 0; e < kMeshEdges; ++e)
+            if (cv[u][e] != V::INF && V::add(md, ew[u][e]) < dy)
+              m = kmin(m, V::add(kmax(cv[u][e], md), ew[u][e]));
+          if (ideg[u] > kMeshEdges && V::add(md, ew[u][kMeshEdges - 1]) < kmin(dy, m)) {
+            for (int32_t j = kMeshEdges; j < ideg[u]; ++j) {
+              const int2 e = G.in_sw[ioff[u] + j];  // tail, weight
+              if (V::add(md, e.y) >= kmin(dy, m)) break;
+              const int32_t c = ld_relaxed(&Cold[e.x]);
+              if (c != V::INF) m = kmin(m, V::add(kmax(c, md), e.y));
+            }
+          }
+          const int32_t cn = kmax(kmax(cy[u], md), kmin(dy, m));
+          nscan += (unsigned long long)ideg[u];
+          ++nvis;
+          const bool relax_again = !lc || dy < dr[u];
+          if (cn >= dy || dy <= th) {
+            put(&Cnew[x], V::INF, same);
+            ++nfix;
+            hit_now |= x == tgt;
+            push = true;
+            fd = relax_again ? dy : V::INF;
+            y[u] = -1;
+          } else {
+            put(&Cnew[x], cn, same);
+            cy[u] = cn;
+            smd = kmin(smd, dy);
+            sth = kmin(sth, V::add(dy, owm[u]));
+            // label-correcting: relaxed again from its lower D (while in the
+            // first bucket above minD)
+            if (lc && relax_again && dy < V::add(md, G.delta)) {
+              push = true;
+              fd = dy | kOpenRelax;
+              dr[u] = dy;
+            }
+          }
+        }
+        const uint64_t pm = __ballot(push);
+        if (push)
+          s.rel[nF + __popcll(pm & ((1ull << l) - 1ull))] = make_int4(x, fd, ooff[u], odeg[u]);
+        nF += __popcll(pm);
+      }
+      __syncthreads();
+      // the next relax's first edges, on their way during the wait below
+      {
+        const int i = l / kMeshLanes, e = l % kMeshLanes;
+        ahead = false;
+        if (i < nF) {
+          const int4 f = s.rel[i];
+          ahead = (f.y & 0x7fffffff) != V::INF && e < f.w;
+          if (ahead) er = G.out_rec[f.z + e];
+        }
+      }
+      if (tgt >= 0) {
+        const bool h = __ballot(hit_now) != 0ull;
+        if (l == 0)
+          put64(&read_d[w], tagged(ep, (h ? kReadHit : 0) | (full ? kReadFull : 0)), same);
+      }
+      const int32_t flags = await_read();
+      if (lost) break;
+      if (flags & kReadFull) {
+        gave_up = true;
+        break;
+      }
+      hit = (flags & kReadHit) != 0;
+    }
+    if (lost) {
+      if (l == 0) atomicMax(&a.ctl->status, 7);
+      return;
+    }
+    if (gave_up) {
+      if (w == 0 && l == 0) q.redo[inst] = 1;
+      continue;
+    }
+    const long long v0 = wave_sum64((long long)nrel), v1 = wave_sum64((long long)nscan);
+    const long long v2 = wave_sum64((long long)nvis), v3 = wave_sum64((long long)nfix);
+    if (l == 0) {
+      if constexpr (BATCH) {
+        atomicAdd(&a.iscanned[3 * inst], (unsigned long long)v1);
+        atomicAdd(&a.iscanned[3 * inst + 1], (unsigned long long)v2);
+        atomicAdd(&a.iscanned[3 * inst + 2], (unsigned long long)v0);
+        if (w == 0) {
+          a.irounds[inst] = r;
+          if (status) atomicMax(&a.ctl->status, status);
+        }
+      } else {
+        Ctl *c = a.ctl;
+        atomicAdd((unsigned long long *)&c->relaxed, (unsigned long long)v0);
+        atomicAdd((unsigned long long *)&c->scanned, (unsigned long long)v1);
+        atomicAdd((unsigned long long *)&c->open_visits, (unsigned long long)v2);
+        // the source is settled too
+        atomicAdd((unsigned long long *)&c->settled, (unsigned long long)(v3 + (w == 0 ? 1 : 0)));
+        if (w == 0) {
+          c->rounds = r;
+          c->status = status;
+          c->target_id = tgt;
+          c->target_hit = hit ? 1 : 0;
+        }
+      }
+    }
+  }
+}
+
+// Waves per team: one per kMeshPerWave vertices (a 66 x 66 grid takes 0.64 ms
+// on 8 waves, 0.74 on 4, 0.77 in one workgroup), at most 64 (a lane reads one
+// wave's words; a 1024 x 1024 grid takes 22.4 ms on 64, 27.8 on 32).  All
+// teams together kMeshWavesPerCu waves per compute unit: 64 solves of a 384 x
+// 384 grid take 4.8 ms at 8, 5.3 at 4 and 11.5 at 2 (seats fill up), 5.8 in
+// one workgroup each.
+constexpr int32_t kMeshPerWave = 512;
+constexpr int kMeshWavesPerCu = 8;
+
+// Teams for this solve, or false: the one-workgroup kernel takes it.
+template <class V, bool BATCH>
+static bool mesh_plan(const RoundArgs &a, const LaunchGeom &geo, int32_t max_n, MeshArgs &q,
+                      int *seats, hipError_t *err) {
+  static std::atomic<int> known{0};  // co-resident blocks per compute unit
+  int occ = known.load();
+  if (occ == 0) {
+    *err = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &occ, (const void *)mesh_rounds_kernel<V, BATCH, 4>, SSSP_WAVE, 0);
+    if (*err != hipSuccess || occ < 1) return false;
+    known.store(occ);
+  }
+  // More instances than half the compute units: a workgroup each fills the
+  // chip with less traffic (256 solves of a 256 x 256 grid: 4.4 ms there, 7.7
+  // in teams; 128 of them: 3.6 and 3.3).
+  if (2 * a.num_inst > geo.cus) return false;
+  const int per_cu = occ < kMeshWavesPerCu ? occ : kMeshWavesPerCu;
+  const int64_t blocks = (int64_t)per_cu * (geo.blocks < geo.cus ? geo.blocks : geo.cus);
+  // the redo words lie in the per-block partials, the team words in the
+  // barrier flags, the mailboxes in the open lists' payload
+  if (a.num_inst > kParts * kMaxBlocks) return false;
+  int lw = 0;
+  while (lw < 6 && ((int64_t)2 << lw) * kMeshPerWave <= (int64_t)max_n) ++lw;
+  for (; lw >= 1; --lw) {
+    const int64_t W = (int64_t)1 << lw;
+    int64_t teams = blocks / (8 * W) * 8;  // whole sets of eight teams
+    if (teams > a.num_inst) teams = a.num_inst;
+    if (teams < a.num_inst) continue;  // smaller teams, one per instance
+    if (teams * W * W * kBox * 8 > (int64_t)kOXMem * 4 * a.total) continue;
+    if (2 * W * teams * 8 > (int64_t)kMaxBlocks * kFlagStride * 4) continue;
+    q.lw = lw;
+    q.teams = (int32_t)teams;
+    q.words = (unsigned long long *)a.flags;
+    q.box0 = (unsigned long long *)a.open_x0[0];
+    q.box1 = (unsigned long long *)a.open_x1[0];
+    q.redo = a.part;
+    // two seats a lane where a wavefront of about 4 sqrt(n) open vertices
+    // fills at most 3/5 of them
+    *seats = 16.0 * max_n <= (0.6 * 2 * SSSP_WAVE * W) * (0.6 * 2 * SSSP_WAVE * W) ? 2 : 4;
+    return true;
+  }
+  return false;
+}
+
+template <class V, bool BATCH>
+static hipError_t launch_mesh_t(const RoundArgs &a, const LaunchGeom &geo, int32_t max_n,
+                                const KernelTimer *timer, Launcher &L, const int32_t **redo) {
+  *redo = nullptr;
+  hipError_t e = hipSuccess;
+  MeshArgs q;
+  int seats = 4;
+  if (a.scope_all || !mesh_plan<V, BATCH>(a, geo, max_n, q, &seats, &e)) return e;
+  RoundArgs arg = a;
+  void *params[] = {&arg, &q};
+  int bx = (max_n + 1023) / 1024;
+  if (bx > 2048) bx = 2048;
+  if ((e = launch_kernel(L, (const void *)mesh_init_kernel<V, BATCH>,
+                         dim3((unsigned)bx, (unsigned)a.num_inst), dim3(256), params, false)) !=
+      hipSuccess)
+    return e;
+  if (L.graph) timer = nullptr;
+  if (timer && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
+  const unsigned grid = (unsigned)(((q.teams + 7) / 8) << q.lw) * 8u;
+  const void *fn = seats == 2 ? (const void *)mesh_rounds_kernel<V, BATCH, 2>
+                              : (const void *)mesh_rounds_kernel<V, BATCH, 4>;
+  if ((e = launch_kernel(L, fn, dim3(grid), dim3(SSSP_WAVE), params, true)) != hipSuccess)
+    return e;
+  if (timer && (e = hipEventRecord(timer->stop, L.stream)) != hipSuccess) return e;
+  *redo = q.redo;
+  return hipSuccess;
+}
+
+hipError_t launch_mesh(bool f32, bool batch, const RoundArgs &a, const LaunchGeom &geo,
+                       int32_t max_n, const KernelTimer *timer, Launcher &L,
+                       const int32_t **redo) {
+  if (f32)
+    return batch ? launch_mesh_t<KeyF32, true>(a, geo, max_n, timer, L, redo)
+                 : launch_mesh_t<KeyF32, false>(a, geo, max_n, timer, L, redo);
+  return batch ? launch_mesh_t<KeyI32, true>(a, geo, max_n, timer, L, redo)
+               : launch_mesh_t<KeyI32, false>(a, geo, max_n, timer, L, redo);
+}
+
+}  // namespace sssp

@@ -1938,8 +1938,13 @@ static hipError_t launch_solve_t(const RoundArgs &a, int32_t *pred, const Launch
   if (geo.blocks > kMaxBlocks) return hipErrorInvalidConfiguration;
   if (max_n <= geo.small_n)
     return launch_small(V::INF == KeyF32::INF, BATCH, a, pred, max_n, timer, L);
-  if (geo.wg && !a.scope_all)
-    return launch_wg(V::INF == KeyF32::INF, BATCH, a, pred, geo, istat, max_n, timer, L);
+  if (geo.wg && !a.scope_all) {
+    const int32_t *redo = nullptr;
+    if (geo.wg == 2 && (e = launch_mesh(V::INF == KeyF32::INF, BATCH, a, geo, max_n, timer, L,
+                                        &redo)) != hipSuccess)
+      return e;
+    return launch_wg(V::INF == KeyF32::INF, BATCH, a, pred, geo, istat, max_n, timer, L, redo);
+  }
   RoundArgs arg = a;
   void *params[] = {&arg};
   {

@@ -160,7 +160,9 @@ struct LaunchGeom {
   int blocks;  // persistent grid size (co-resident)
   int cus;
   int small_n = 0;  // solves of at most this many vertices run in one workgroup each, state in LDS
-  int wg = 0;       // every instance in a workgroup of its own (scope OPEN only)
+  // scope OPEN only: 1: every instance in a workgroup of its own; 2: by a
+  // team of workgroups where that fits
+  int wg = 0;
 };
 
 // Largest graph the one-workgroup solver holds in LDS.
@@ -219,10 +221,18 @@ hipError_t round_kernel_occupancy(bool f32, bool batch, int *blocks_per_cu);
 // device current).
 constexpr size_t kScratchBytes = (size_t)64 << 20;
 hipError_t scratch_address(void **ptr);
-// every instance's rounds in a workgroup of its own (C scope OPEN), then the emit pass
+// every instance's rounds in a workgroup of its own (C scope OPEN), then the
+// emit pass; redo (nullable): per instance, whether to run it at all (the
+// team kernel before it has run the others)
 hipError_t launch_wg(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
                      const LaunchGeom &geo, long long *istat, int32_t max_n,
-                     const KernelTimer *timer, Launcher &L);
+                     const KernelTimer *timer, Launcher &L, const int32_t *redo);
+// every instance's rounds by a team of single-wave workgroups (C scope OPEN);
+// *redo: the instances launch_wg has to run, or null: nothing was launched
+// (teams do not fit)
+hipError_t launch_mesh(bool f32, bool batch, const RoundArgs &a, const LaunchGeom &geo,
+                       int32_t max_n, const KernelTimer *timer, Launcher &L,
+                       const int32_t **redo);
 // every instance (max_n <= kSmallN vertices) in a workgroup of its own with its
 // state in LDS, costs and parents included
 hipError_t launch_small(bool f32, bool batch, const RoundArgs &a, int32_t *pred, int32_t max_n,

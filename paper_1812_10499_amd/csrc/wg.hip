@@ -54,10 +54,10 @@ __device__ __forceinline__ void push_rel(WgLds &s, int32_t *F, int32_t *FD, int3
 }
 
 template <class V, bool BATCH>
-__global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a) {
+__global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32_t *redo) {
   __shared__ WgLds s;
   const int tid = threadIdx.x;
-  if (blockIdx.x == 0 && tid == 0) {
+  if (!redo && blockIdx.x == 0 && tid == 0) {
     // the control block the emit pass and the host read
     Ctl *c = a.ctl;
     c->front_ctr[0] = c->front_ctr[1] = 0ull;
@@ -70,6 +70,7 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a) {
     c->status = 0;
   }
   for (int inst = blockIdx.x; inst < a.num_inst; inst += gridDim.x) {
+    if (redo && !redo[inst]) continue;
     int32_t sb = 0, gi = 0, src = a.source, n = a.g.n;
     if constexpr (BATCH) {
       const InstDev id = a.insts[inst];
@@ -382,11 +383,12 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a) {
 template <class V, bool BATCH>
 static hipError_t launch_wg_t(const RoundArgs &a, int32_t *pred, const LaunchGeom &geo,
                               long long *istat, int32_t max_n, const KernelTimer *timer,
-                              Launcher &L) {
+                              Launcher &L, const int32_t *redo) {
   hipError_t e;
   if (a.scope_all) return hipErrorInvalidValue;  // the live pass is not here
   RoundArgs arg = a;
-  void *params[] = {&arg};
+  void *params[] = {&arg, &redo};
+  if (redo) timer = nullptr;  // (the team kernel was the timed one)
   int blocks = a.num_inst < geo.blocks ? a.num_inst : geo.blocks;
   if (blocks < 1) blocks = 1;
   if (L.graph) timer = nullptr;
@@ -400,12 +402,12 @@ static hipError_t launch_wg_t(const RoundArgs &a, int32_t *pred, const LaunchGeo
 
 hipError_t launch_wg(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
                      const LaunchGeom &geo, long long *istat, int32_t max_n,
-                     const KernelTimer *timer, Launcher &L) {
+                     const KernelTimer *timer, Launcher &L, const int32_t *redo) {
   if (f32)
-    return batch ? launch_wg_t<KeyF32, true>(a, pred, geo, istat, max_n, timer, L)
-                 : launch_wg_t<KeyF32, false>(a, pred, geo, istat, max_n, timer, L);
-  return batch ? launch_wg_t<KeyI32, true>(a, pred, geo, istat, max_n, timer, L)
-               : launch_wg_t<KeyI32, false>(a, pred, geo, istat, max_n, timer, L);
+    return batch ? launch_wg_t<KeyF32, true>(a, pred, geo, istat, max_n, timer, L, redo)
+                 : launch_wg_t<KeyF32, false>(a, pred, geo, istat, max_n, timer, L, redo);
+  return batch ? launch_wg_t<KeyI32, true>(a, pred, geo, istat, max_n, timer, L, redo)
+               : launch_wg_t<KeyI32, false>(a, pred, geo, istat, max_n, timer, L, redo);
 }
 
 }  // namespace sssp
