@@ -215,7 +215,7 @@ typedef struct {
  * round kernel that runs.
  */
 typedef enum {
-  SSSP_KERNEL_PERSISTENT = 0, /* rounds_kernel: cooperative grid, grid barriers */
+  SSSP_KERNEL_PERSISTENT = 0, /* cooperative grid, grid or team barriers */
   SSSP_KERNEL_WORKGROUP = 1,  /* one workgroup, or one team of workgroups, per solve */
   SSSP_KERNEL_SMALL = 2       /* small_rounds_kernel: one workgroup per solve, state in LDS */
 } sssp_kernel;
@@ -419,7 +419,11 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
  *                trees), 1 always, negative never.  By default, few
  *                instances (at most half as many as compute units) run each
  *                in a team of cooperating workgroups instead; one whose open
- *                set outgrows its team runs again in one workgroup.
+ *                set outgrows its team runs again in one workgroup.  Also by
+ *                default, solves whose graphs all run C scope ALL and have
+ *                no vertex of more than 256 edges run in teams of workgroups
+ *                that own every vertex (a non-zero wg: on the grid-wide
+ *                kernel).
  */
 typedef struct {
   int32_t blocks;

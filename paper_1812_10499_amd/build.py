@@ -9,9 +9,9 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 SO = os.path.join(PKG, "libsssp.so")
-SOURCES = ["api.hip", "solve.hip", "small.hip", "wg.hip", "mesh.hip", "pred.hip", "build_csr.hip",
+SOURCES = ["api.hip", "solve.hip", "small.hip", "wg.hip", "mesh.hip", "dense.hip", "pred.hip", "build_csr.hip",
            "backward.hip"]
-HEADERS = ["sssp_dev.h", "sssp_kernels.h"]
+HEADERS = ["sssp_dev.h", "sssp_kernels.h", "team.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -182,6 +182,7 @@ sssp_status resolve_launch(DevWS &w, bool f32, bool batch, const sssp_launch *L,
   if (L && L->small_n) geo->small_n = L->small_n < 0 ? 0 : (L->small_n < kSmallN ? L->small_n : kSmallN);
   const int wg = L ? L->wg : 0;
   geo->wg = wg > 0 ? 1 : (wg == 0 && low_spread ? 2 : 0);
+  geo->dense = wg == 0 ? 1 : 0;
   return SSSP_OK;
 }
 
@@ -212,6 +213,9 @@ bool scope_all_of(const sssp_csr *g) {
   if (g->scope == SSSP_SCOPE_AUTO) return g->m > 0 && !low_spread(g);
   return g->scope == SSSP_SCOPE_ALL;
 }
+
+// C scope ALL and no hubs: solves run in teams that own every vertex.
+bool dense_graph(const sssp_csr *g) { return scope_all_of(g) && g->deg_max <= kDenseDegree; }
 
 // SSSP_RELAX_AUTO: label-correcting relax in buckets of 0.4 w_max on graphs
 // of low degree spread (largest total degree below 3m/n: the AUTO scope's
@@ -782,6 +786,7 @@ static void single_fill(const sssp_csr *g, int32_t source, int32_t target, void 
   a.target = target;
   a.scope_all = a.g.all;
   a.any_lc = a.g.lc;
+  a.dense = dense_graph(g) ? 1 : 0;
 }
 
 static sssp_status single_args(DevWS &ws, const sssp_csr *g, int32_t source, int32_t target,
@@ -900,7 +905,9 @@ static sssp_status batch_args(DevWS &ws, const sssp_csr *graphs, int32_t num_gra
   a.max_rounds = round_limit(max_n);
   a.target = -1;
   a.D = (int32_t *)cost;
+  a.dense = 1;
   for (int32_t i = 0; i < num_inst; ++i) {
+    if (!dense_graph(&graphs[inst_graph[i]])) a.dense = 0;
     if (relax_correcting(&graphs[inst_graph[i]])) a.any_lc = 1;
     if (scope_all_of(&graphs[inst_graph[i]])) a.scope_all = 1;
   }
@@ -1217,6 +1224,7 @@ static sssp_status plan_build(const sssp_csr *graphs, int32_t num_graphs,
       a.target = -1;
       a.scope_all = a.g.all;
       a.any_lc = a.g.lc;
+      a.dense = dense_graph(g) ? 1 : 0;
       a.ctl = ctls + i;
       p->seq.push_back(a);
       p->seq_n.push_back(g->n);

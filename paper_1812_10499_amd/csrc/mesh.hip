@@ -40,6 +40,7 @@
 
 #include "sssp_dev.h"
 #include "sssp_kernels.h"
+#include "team.h"
 
 namespace sssp {
 
@@ -48,34 +49,6 @@ constexpr int kBox = 16;       // mailbox entries per pair of waves and round
 constexpr int kMeshLanes = 4;  // lanes that share a relax item's out-list
 constexpr int32_t kGiveUp = 0;  // as minD: below every open vertex's D
 constexpr int32_t kReadHit = 1, kReadFull = 2;  // target fixed; seats full
-// A wait ends after this many reads (some seconds; a round takes
-// microseconds) and the solve with an internal error.
-constexpr int kSpinLimit = 1 << 24;
-
-// A store the team's other waves are to read (with agent-scope loads, which
-// pass over the L1): within one XCD it only has to reach the shared L2 (about
-// 440 cycles until done, against 830 for an agent-scope store; with the latter
-// the 1024 x 1024 grid takes 45 ms).
-__device__ __forceinline__ void put(int32_t *p, int32_t v, bool same_l2) {
-  if (same_l2) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void put64(unsigned long long *p, unsigned long long v, bool same_l2) {
-  if (same_l2) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// every store of this wave has reached the point the other waves read
-__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ unsigned long long tagged(unsigned tag, int32_t v) {
-  return ((unsigned long long)tag << 32) | (uint32_t)v;
-}
-
-// A wave's published word: the round's low two bits (no wave is more than one
-// round ahead of another), minD's key and thr's (non-negative).
-__device__ __forceinline__ unsigned long long offers(unsigned ep, int32_t md, int32_t th) {
-  return ((unsigned long long)(ep & 3u) << 62) | ((unsigned long long)(uint32_t)md << 31) |
-         (unsigned long long)(uint32_t)th;
-}
 
 // The wave of the team that owns vertex y (W = 1 << lw): Murmur3's 32-bit
 // finalizer (Appleby), low bits.  A plain multiplicative hash sends all the
@@ -171,17 +144,6 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
   const int lp = l < W ? l : 0;  // the wave whose words this lane reads
   unsigned ep = 1;               // rounds over all of the team's instances: the tag
   bool lost = false;
-  // the published words of this round
-  auto await_offers = [&]() -> unsigned long long {
-    unsigned long long x = 0;
-    int spins = 0;
-    do {
-      x = ld_relaxed64(&pub[lp]);
-      lost = ++spins > kSpinLimit;
-    } while (!lost && __ballot((unsigned)(x >> 62) != (ep & 3u)));
-    asm volatile("" ::: "memory");  // nothing below is read before the words
-    return x;
-  };
   // all "D read" words of this round: the union of their flags
   auto await_read = [&]() -> int32_t {
     unsigned long long x = 0;
@@ -199,10 +161,10 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
   // round 1 of the words: whether the team shares an XCD, and so an L2
   bool same = false;
   {
-    const int32_t xcc = (int32_t)(__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xffu);
+    const int32_t xcc = xcd_id();
     if (l == 0) put64(&pub[w], offers(ep, xcc + 1, 0), false);
-    const unsigned long long x = await_offers();
-    same = __ballot((int32_t)((x >> 31) & 0x7fffffffu) != xcc + 1) == 0ull;
+    const unsigned long long x = await_offers(pub, lp, ep, &lost);
+    same = __ballot(offers_md(x) != xcc + 1) == 0ull;
     if (l == 0) put64(&read_d[w], tagged(ep, 0), false);
     await_read();
     if (lost) {
@@ -304,9 +266,9 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
       stores_done();
       if (l == 0) put64(&pub[w], offers(ep, md, th), same);
       {
-        const unsigned long long x = await_offers();
-        md = wave_min((int32_t)((x >> 31) & 0x7fffffffu));
-        th = wave_min((int32_t)(x & 0x7fffffffu));
+        const unsigned long long x = await_offers(pub, lp, ep, &lost);
+        md = wave_min(offers_md(x));
+        th = wave_min(offers_th(x));
       }
       if (lost) break;
       if (md == kGiveUp || md == V::INF) {  // (every wave alike)

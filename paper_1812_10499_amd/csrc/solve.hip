@@ -1945,6 +1945,13 @@ static hipError_t launch_solve_t(const RoundArgs &a, int32_t *pred, const Launch
       return e;
     return launch_wg(V::INF == KeyF32::INF, BATCH, a, pred, geo, istat, max_n, timer, L, redo);
   }
+  if (a.dense && geo.dense) {
+    bool done = false;
+    if ((e = launch_dense(V::INF == KeyF32::INF, BATCH, a, geo, max_n, timer, L, &done)) !=
+        hipSuccess)
+      return e;
+    if (done) return launch_pred(V::INF == KeyF32::INF, BATCH, a, pred, geo, istat, max_n, L);
+  }
   RoundArgs arg = a;
   void *params[] = {&arg};
   {

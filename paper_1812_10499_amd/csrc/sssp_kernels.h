@@ -142,7 +142,12 @@ struct RoundArgs {
   // (INF before its first relax)
   int32_t *DR;
   int32_t any_lc;  // some graph of the solve relaxes label-correcting
+  // every graph of the solve runs C scope ALL and has no vertex of more than
+  // kDenseDegree edges (read by the host's choice of kernel)
+  int32_t dense;
 };
+
+constexpr int32_t kDenseDegree = 256;
 
 // Trace record of one round: wall-clock (100 MHz) at the relax start, block
 // 0's arrival at and release from each of the two barriers, the list sizes
@@ -163,6 +168,7 @@ struct LaunchGeom {
   // scope OPEN only: 1: every instance in a workgroup of its own; 2: by a
   // team of workgroups where that fits
   int wg = 0;
+  int dense = 0;  // solves with RoundArgs::dense run in teams that own every vertex
 };
 
 // Largest graph the one-workgroup solver holds in LDS.
@@ -227,6 +233,11 @@ hipError_t scratch_address(void **ptr);
 hipError_t launch_wg(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
                      const LaunchGeom &geo, long long *istat, int32_t max_n,
                      const KernelTimer *timer, Launcher &L, const int32_t *redo);
+// every instance's rounds by a team of workgroups with every vertex owned by a
+// thread (a.dense); *done: false, nothing was launched (an instance is too
+// large)
+hipError_t launch_dense(bool f32, bool batch, const RoundArgs &a, const LaunchGeom &geo,
+                        int32_t max_n, const KernelTimer *timer, Launcher &L, bool *done);
 // every instance's rounds by a team of single-wave workgroups (C scope OPEN);
 // *redo: the instances launch_wg has to run, or null: nothing was launched
 // (teams do not fit)
