@@ -74,6 +74,12 @@ struct DenseLds {
   unsigned long long relaxed, scanned, visits, settled;
 };
 
+// a pointer all lanes hold alike, in scalar registers
+template <class T>
+__device__ __forceinline__ T *scalar_ptr(T *p) {
+  return (T *)(uintptr_t)readlane64((int64_t)(uintptr_t)p, 0);
+}
+
 template <class V, bool BATCH>
 __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArgs q) {
   __shared__ DenseLds s;
@@ -104,7 +110,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
       if (l == 0) put64(&words[j], offers(ep, md, th), same);
       bool lo = false;
       md = th = 0x7fffffff;
-      if (K <= SSSP_WAVE) {
+      if (BATCH || K <= SSSP_WAVE) {  // (a batch's teams are of one XCD)
         const unsigned long long x = await_offers(words, l < K ? l : 0, ep, &lo);
         md = offers_md(x);
         th = offers_th(x);
@@ -141,9 +147,9 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
       }
     }
     __syncthreads();
-    md = s.md;
-    th = s.th;
-    lost = s.lost != 0;
+    md = __builtin_amdgcn_readfirstlane(s.md);
+    th = __builtin_amdgcn_readfirstlane(s.th);
+    lost = __builtin_amdgcn_readfirstlane(s.lost) != 0;
   };
   {
     // round 1 of the words: whether the team shares an XCD, and so an L2
@@ -164,7 +170,23 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
       gi = id.graph;
       src = id.source;
     }
-    const GraphDev G = graph_of<BATCH>(a, gi);
+    GraphDev G = graph_of<BATCH>(a, gi);
+    if constexpr (BATCH) {
+      // read from a table, so in vector registers, though alike in all lanes
+      sb = __builtin_amdgcn_readfirstlane(sb);
+      src = __builtin_amdgcn_readfirstlane(src);
+      G.n = __builtin_amdgcn_readfirstlane(G.n);
+      G.lc = __builtin_amdgcn_readfirstlane(G.lc);
+      G.all = __builtin_amdgcn_readfirstlane(G.all);
+      G.delta = __builtin_amdgcn_readfirstlane(G.delta);
+      G.out_rec = scalar_ptr(G.out_rec);
+      G.vrec = scalar_ptr(G.vrec);
+      G.vin = scalar_ptr(G.vin);
+      G.in_sw = scalar_ptr(G.in_sw);
+      G.out_wmin = scalar_ptr(G.out_wmin);
+      G.out_off = scalar_ptr(G.out_off);
+      G.rank = scalar_ptr(G.rank);
+    }
     const int n = G.n;
     const bool lc = G.lc != 0, all = G.all != 0;
     int32_t tgt = BATCH ? -1 : a.target;
@@ -508,8 +530,9 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
       }
     }
     __syncthreads();
-    inst = s.next;
-    lost = s.lost != 0;
+    // (uniform: the graph's fields then sit in scalar registers)
+    inst = __builtin_amdgcn_readfirstlane(s.next);
+    lost = __builtin_amdgcn_readfirstlane(s.lost) != 0;
     __syncthreads();
   }
   if (lost && tid == 0) atomicMax(&a.ctl->status, 7);
