@@ -23,8 +23,7 @@ enum Slot {
   S_IMIN, S_ITHR, S_IROUNDS, S_ISCAN, S_DEGEN, S_LVL, S_FLAG, S_SPRED, S_ISTAT,
   S_GTAB, S_ITAB,
   S_BK_COLS, S_BK_HIST, S_BK_TAIL, S_BK_HEAD, S_BK_DEG, S_BK_STATUS,
-  S_BW_ACC, S_BW_LV, S_BW_LI, S_BW_LOFF, S_BW_CTL, S_BW_GOFF, S_BW_GINST, S_BW_EBASE,
-  S_BW_CS, S_BW_LACC,
+  S_BW_ACC, S_BW_PAR, S_BW_WORD, S_BW_CTL, S_BW_TAB,
   S_TRACE, S_FLAGS, S_PART, S_D64, S_FX, S_OX0, S_OX1, S_LV0, S_LV1, S_DR, S_INSTOF, S_IDEAD,
   NSLOTS
 };
@@ -1424,30 +1423,18 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
   b.total = (int32_t)total;
   b.pred = pred;
   b.gcost = grad_cost;
-  GraphDev *dg;
-  InstDev *di;
-  int32_t *goff, *ginst, *ebase;
-  unsigned int *bctl;
-  if ((s = ws_arr(ws, S_GTAB, (size_t)num_graphs, &dg))) return s;
-  if ((s = ws_arr(ws, S_ITAB, (size_t)num_inst, &di))) return s;
-  if ((s = ws_arr(ws, S_BW_ACC, (size_t)total, &b.acc))) return s;
-  if ((s = ws_arr(ws, S_BW_LV, (size_t)total, &b.lv_v))) return s;
-  if ((s = ws_arr(ws, S_BW_LI, (size_t)total, &b.lv_i))) return s;
-  if ((s = ws_arr(ws, S_BW_LOFF, (size_t)total + 2, &b.lv_off))) return s;
-  if ((s = ws_arr(ws, S_BW_CS, (size_t)total, &b.lv_cs))) return s;
-  if ((s = ws_arr(ws, S_BW_LACC, (size_t)total, &b.lv_acc))) return s;
-  if ((s = ws_arr(ws, S_BW_CTL, 8, &bctl))) return s;
-  if ((s = ws_arr(ws, S_BW_GOFF, (size_t)num_graphs + 1, &goff))) return s;
-  if ((s = ws_arr(ws, S_BW_GINST, (size_t)num_inst, &ginst))) return s;
-  if ((s = ws_arr(ws, S_BW_EBASE, (size_t)num_graphs + 1, &ebase))) return s;
-  if ((s = ws_arr(ws, S_FLAGS, (size_t)kMaxBlocks * kFlagStride, &b.flags))) return s;
-  b.go = bctl;
-  b.ctr = bctl + 1;
-  b.nlevels = (int32_t *)(bctl + 2);
-  b.graphs = dg;
-  b.insts = di;
+  b.grad_w = grad_w;
+  b.num_graphs = num_graphs;
+  b.total_m = (int32_t)total_m;
+  // the tables, sent with one copy
   const size_t tab_bytes = sizeof(GraphDev) * num_graphs + sizeof(InstDev) * num_inst +
-                           sizeof(int32_t) * (3 * (size_t)num_graphs + 2 + num_inst) + 64;
+                           sizeof(int32_t) * (3 * ((size_t)num_graphs + 1) + num_inst);
+  char *tab;
+  if ((s = ws_arr(ws, S_BW_TAB, tab_bytes, &tab))) return s;
+  if ((s = ws_arr(ws, S_BW_ACC, (size_t)total, &b.acc))) return s;
+  if ((s = ws_arr(ws, S_BW_PAR, (size_t)total, &b.par))) return s;
+  if ((s = ws_arr(ws, S_BW_WORD, (size_t)total, &b.word))) return s;
+  if ((s = ws_arr(ws, S_BW_CTL, kBackCtl, &b.ctl))) return s;
   void *hp;
   if ((s = pinned_get(ws, tab_bytes, &hp))) return s;
   GraphDev *hg = (GraphDev *)hp;
@@ -1455,6 +1442,14 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
   int32_t *hgoff = (int32_t *)(hi + num_inst);
   int32_t *hginst = hgoff + num_graphs + 1;
   int32_t *hebase = hginst + num_inst;
+  int32_t *hbbase = hebase + num_graphs + 1;
+  const auto at = [&](const void *h) { return tab + ((const char *)h - (const char *)hp); };
+  b.graphs = (const GraphDev *)at(hg);
+  b.insts = (const InstDev *)at(hi);
+  b.goff = (const int32_t *)at(hgoff);
+  b.ginst = (const int32_t *)at(hginst);
+  b.ebase = (const int32_t *)at(hebase);
+  b.bbase = (const int32_t *)at(hbbase);
   for (int32_t gi = 0; gi < num_graphs; ++gi) hg[gi] = graph_dev(&graphs[gi]);
   int32_t base = 0;
   for (int32_t i = 0; i < num_inst; ++i) {
@@ -1467,36 +1462,29 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
   // instances grouped by graph, in instance order within a graph
   for (int32_t gi = 0; gi <= num_graphs; ++gi) hgoff[gi] = 0;
   for (int32_t i = 0; i < num_inst; ++i) hgoff[inst_graph[i] + 1]++;
-  for (int32_t gi = 0; gi < num_graphs; ++gi) hgoff[gi + 1] += hgoff[gi];
+  int32_t max_inst = 0;
+  for (int32_t gi = 0; gi < num_graphs; ++gi) {
+    if (hgoff[gi + 1] > max_inst) max_inst = hgoff[gi + 1];
+    hgoff[gi + 1] += hgoff[gi];
+  }
   {
     std::vector<int32_t> fill(hgoff, hgoff + num_graphs);
     for (int32_t i = 0; i < num_inst; ++i) hginst[fill[inst_graph[i]]++] = i;
   }
-  int32_t eb = 0;
-  for (int32_t gi = 0; gi < num_graphs; ++gi) {
-    hebase[gi] = eb;
+  int64_t eb = 0, bb = 0;
+  for (int32_t gi = 0; gi <= num_graphs; ++gi) {
+    hebase[gi] = (int32_t)eb;
+    hbbase[gi] = (int32_t)bb;
+    if (gi == num_graphs) break;
     eb += graphs[gi].m;
+    bb += (graphs[gi].n + (int64_t)kBackBlock - 1) / kBackBlock;
   }
-  hebase[num_graphs] = eb;
-  LaunchGeom geo;
-  if ((s = geometry(ws, true, true, &geo))) return s;
-  {
-    // deep trees (graphs of low degree spread): each instance in a workgroup
-    const int wg = ws.cfg.wg;
-    geo.wg = wg > 0 || (wg == 0 && all_low_spread(graphs, inst_graph, num_inst)) ? 1 : 0;
-  }
+  if (bb > INT_MAX) return SSSP_ERR_ARG;  // (not in memory: half a trillion vertices)
+  b.blocks = (int32_t)bb;
   HIPCHK(hipStreamWaitEvent(stream, ws.last, 0));
-  HIPCHK(hipMemcpyAsync(dg, hg, sizeof(GraphDev) * num_graphs, hipMemcpyHostToDevice, stream));
-  HIPCHK(hipMemcpyAsync(di, hi, sizeof(InstDev) * num_inst, hipMemcpyHostToDevice, stream));
-  HIPCHK(hipMemcpyAsync(goff, hgoff, sizeof(int32_t) * (num_graphs + 1), hipMemcpyHostToDevice,
-                        stream));
-  HIPCHK(hipMemcpyAsync(ginst, hginst, sizeof(int32_t) * num_inst, hipMemcpyHostToDevice,
-                        stream));
-  HIPCHK(hipMemcpyAsync(ebase, hebase, sizeof(int32_t) * (num_graphs + 1),
-                        hipMemcpyHostToDevice, stream));
+  HIPCHK(hipMemcpyAsync(tab, hp, tab_bytes, hipMemcpyHostToDevice, stream));
   HIPCHK(hipEventRecord(ws.staged, stream));
-  HIPCHK(launch_backward(b, geo, goff, ginst, ebase, num_graphs, (int32_t)total_m, grad_w,
-                         stream));
+  HIPCHK(launch_backward(b, max_inst, stream));
   HIPCHK(hipEventRecord(ws.last, stream));
   return SSSP_OK;
 }

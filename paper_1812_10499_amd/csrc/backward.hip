@@ -1,364 +1,356 @@
 // Backward pass of the shortest-path costs with respect to edge weights.
 //
-// The source of an instance is the root of its tree whatever its pred entry
-// says: it is never taken as a child, and no edge into it gets a gradient.
-// Every other vertex has one parent entry, so a walk down from the root
-// meets each vertex at most once (a vertex on a parent cycle that avoids the
-// root is reachable from no vertex outside that cycle), and the level lists
-// never hold more than the instance's n entries.
-//
 // With cost_i[x] the weight sum along the pred-tree path from instance i's
 // source to x, L = sum_i sum_x g_i[x] * cost_i[x] has
 //   dL/dw[e] = sum_i [e == pred_i[head(e)]] * acc_i[head(e)],
 //   acc_i[y] = g_i[y] + sum over tree children c of y of acc_i[c].
-// The tree's children of y are the heads of y's out-edges e with
-// pred[head(e)] == e, so no child lists are built: a top-down pass records
-// the tree level by level (persistent kernel, one grid barrier per level),
-// and a bottom-up pass computes acc deepest level first, each vertex adding
-// its children in edge-id order (or, for deep trees, each instance in a
-// workgroup of its own).  A final edge-parallel kernel sums the instances of
-// each graph in instance order.  Every sum has a fixed order,
-// so the result is deterministic.
+// The children of y are the heads of y's out-edges e with pred[head(e)] == e,
+// added in edge order, and the instances of a graph are summed in instance
+// order, so every sum has a fixed order and the result is deterministic.
+//
+// The source of an instance is the root of its tree whatever its pred entry
+// says: it is never taken as a child, and no edge into it gets a gradient.
+// Only vertices whose parents lead to the root contribute (a pred array that
+// the solver did not write may hold parent cycles and stray trees).
+//
+// There are no levels and no barriers.  A vertex's sum is complete when its
+// last child's is, so every leaf starts a walk towards the root and each
+// vertex is carried on by the child that arrives last; the work is one walk
+// over the tree, in whatever order its parts are ready, and only the deepest
+// path is serial.  A level list with a barrier per level spends most of its
+// time in the barriers (a 512 x 512 grid has 1000 levels of 260 vertices).
 #include "sssp_dev.h"
 #include "sssp_kernels.h"
+#include "team.h"
 
 namespace sssp {
 
 constexpr int BBS = kBackBlock;
+constexpr int kBackIn = 8;      // in-edges of a vertex held in registers
+constexpr int kBackChunk = 8;   // instances per block of the parent pass
+constexpr int kBackScan = 16;   // out-edges one lane looks through by itself
 
-// acc = 0 everywhere, so a vertex whose parent entry names an edge from
-// outside the tree contributes nothing
-__global__ void bw_zero_kernel(BackArgs a) {
-  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.total;
-       i += gridDim.x * blockDim.x)
-    a.acc[i] = 0.0f;
+// BackArgs::ctl: a flag, and the number of vertices walked in kBackSums parts
+constexpr int kBackSums = kBackCtl / kBackStride - 1;
+
+// BackArgs::par of a vertex without a parent
+enum : int32_t {
+  kNoParent = -1,     // not the source: its subtree counts for nothing
+  kUnderRoot = -2,    // a child of the source (whose own sum nobody needs)
+  kRoot = -3,
+};
+
+__global__ __launch_bounds__(BBS) void bw_zero_kernel(BackArgs a) {
+  const int64_t step = (int64_t)gridDim.x * BBS, i0 = (int64_t)blockIdx.x * BBS + threadIdx.x;
+  for (int64_t i = i0; i < a.total; i += step) a.word[i] = 0ull;
+  for (int64_t i = i0; i < a.total_m; i += step) a.grad_w[i] = 0.0f;
+  if (i0 < kBackCtl) a.ctl[i0] = 0u;
 }
 
-__global__ void bw_init_kernel(BackArgs a) {
-  for (int i = threadIdx.x; i < a.num_inst; i += blockDim.x) {
-    const InstDev id = a.insts[i];
-    a.lv_v[i] = id.sbase + id.source;
-    a.lv_i[i] = i;
+// The graph whose vertices block b of the per-vertex passes covers.
+__device__ __forceinline__ int32_t block_graph(const BackArgs &a, int32_t b) {
+  int32_t lo = 0, hi = a.num_graphs;  // bbase[lo] <= b < bbase[hi]
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (a.bbase[mid] <= b) lo = mid;
+    else hi = mid;
   }
-  for (int b = threadIdx.x; b < kMaxBlocks; b += blockDim.x) a.flags[b * kFlagStride] = 0u;
-  if (threadIdx.x == 0) {
-    *a.go = 0u;
-    *a.ctr = (unsigned int)a.num_inst;
-    a.lv_off[0] = 0;
-    a.lv_off[1] = a.num_inst;
-    *a.nlevels = 0;
+  return lo;
+}
+
+// A vertex's first in-edges (id and tail); slots past the list's end hold an
+// id that no entry names.
+struct InEdges {
+  int32_t deg, eid[kBackIn], src[kBackIn];
+  __device__ __forceinline__ void load(const GraphDev &G, int32_t y, bool tails) {
+    const int32_t o = G.u_in_off[y];
+    deg = G.u_in_off[y + 1] - o;
+#pragma unroll
+    for (int q = 0; q < kBackIn; ++q) {
+      eid[q] = q < deg ? G.u_in_eid[o + q] : -1;
+      src[q] = tails && q < deg ? G.u_in_src[o + q] : -1;
+    }
+  }
+};
+
+// the tail of edge e
+__device__ __forceinline__ int32_t edge_tail(const GraphDev &G, int32_t e) {
+  int32_t lo = 0, hi = G.n;  // u_out_off[lo] <= e < u_out_off[hi]
+  while (hi - lo > 1) {
+    const int32_t mid = lo + ((hi - lo) >> 1);
+    if (G.u_out_off[mid] <= e) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// Each vertex's parent and, in the low half of its word, its number of
+// children.  A block holds the in-edges of its vertices in registers and
+// looks the entries of up to kBackChunk instances up in them.
+__global__ __launch_bounds__(BBS) void bw_parent_kernel(BackArgs a) {
+  for (int32_t b = blockIdx.x; b < a.blocks; b += gridDim.x) {
+    const int32_t g = block_graph(a, b);
+    const GraphDev &G = a.graphs[g];
+    const int32_t y = (b - a.bbase[g]) * BBS + (int32_t)threadIdx.x;
+    const int32_t j1 = a.goff[g + 1];
+    int32_t j = a.goff[g] + (int32_t)blockIdx.y * kBackChunk;
+    if (j >= j1 || y >= G.n) continue;
+    InEdges in;
+    in.load(G, y, true);
+    for (; j < j1; j += (int32_t)gridDim.y * kBackChunk) {
+#pragma unroll 4
+      for (int32_t jj = j; jj < (j + kBackChunk < j1 ? j + kBackChunk : j1); ++jj) {
+        const InstDev id = a.insts[a.ginst[jj]];
+        const int32_t e = a.pred[id.sbase + y];
+        int32_t t = -1;
+        if (e >= 0) {
+#pragma unroll
+          for (int q = 0; q < kBackIn; ++q) t = in.eid[q] == e ? in.src[q] : t;
+          if (in.deg > kBackIn && t < 0 && e < G.m && G.u_out_dst[e] == y) t = edge_tail(G, e);
+        }
+        int32_t up = id.sbase + t;
+        if (y == id.source) up = kRoot;
+        else if (t < 0) up = kNoParent;
+        else if (t == id.source) up = kUnderRoot;
+        else atomicAdd((unsigned int *)&a.word[up], 1u);
+        a.par[id.sbase + y] = up;
+      }
+    }
   }
 }
 
-__global__ __launch_bounds__(BBS) void bw_levels_kernel(BackArgs a) {
-  __shared__ uint64_t scan[BBS / SSSP_WAVE + 1];
-  __shared__ unsigned int sbase;
-  const int tid = threadIdx.x;
-  const int nb = gridDim.x, bid = blockIdx.x;
-  unsigned int epoch = 0;
-  // ---- top-down: level L occupies [s, e) of the level list
-  int s = 0, e = a.num_inst, L = 0;
-  while (s < e) {
-    for (int b0 = s + bid * BBS; b0 < e; b0 += nb * BBS) {
-      const int idx = b0 + tid;
-      int32_t x = 0, ins = 0, sb = 0, vx = 0, k0 = 0, k1 = 0, root = -1;
-      const GraphDev *G = nullptr;
-      uint32_t nch = 0;
-      // the children among the first four out-edges (bit q: edge k0 + q)
-      uint32_t cm = 0;
-      int32_t cc[4] = {0, 0, 0, 0};
-      if (idx < e) {
-        x = a.lv_v[idx];
-        ins = a.lv_i[idx];
-        const InstDev id = a.insts[ins];
+// The walk.  The word of a vertex p holds the number of its children (low
+// half) and, with three or more, how many have arrived (high half).  The
+// first of two children swaps its edge id and sum into the word and leaves;
+// the second finds them there.  Of more children, each stores its sum, waits
+// until the store is done and counts itself; the last reads the sums in edge
+// order, alone or (long out-lists) with its whole wave.  An only child just
+// goes on, so a chain costs one load's latency a vertex.
+__global__ __launch_bounds__(BBS) void bw_walk_kernel(BackArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * BBS + threadIdx.x;
+  const int l = lane_id();
+  int32_t v = (int32_t)i, up = kNoParent, steps = 0;
+  bool act = false;
+  float acc = 0.0f;
+  if (i < a.total) {
+    const unsigned long long w = ld_relaxed64(&a.word[i]);
+    up = a.par[i];
+    if (w == 0ull) {
+      act = true;
+      acc = a.gcost[i];
+    } else if (up == kNoParent) {
+      a.ctl[0] = 1u;  // a stray tree
+    }
+  }
+  while (__ballot(act)) {
+    // v's sum is complete: on to its parent p
+    const int32_t p = up;
+    bool many = false;
+    if (act) {
+      ++steps;
+      if (p < 0) {
+        a.acc[v] = acc;
+        act = false;
+      } else {
+        const int32_t e = a.pred[v];
+        unsigned long long w = ld_relaxed64(&a.word[p]);
+        const float g = a.gcost[p];
+        up = a.par[p];
+        if ((long long)w < 0 || (uint32_t)w <= 2u) {
+          a.acc[v] = acc;
+          if ((long long)w >= 0 && (uint32_t)w == 2u)
+            w = __hip_atomic_exchange(&a.word[p],
+                                      ((unsigned long long)(0x80000000u | (uint32_t)e) << 32) |
+                                          (unsigned long long)__float_as_uint(acc),
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if ((long long)w < 0) {
+            const int32_t e2 = (int32_t)((uint32_t)(w >> 32) & 0x7fffffffu);
+            const float s = __uint_as_float((uint32_t)w);
+            acc = __fadd_rn(__fadd_rn(g, e < e2 ? acc : s), e < e2 ? s : acc);
+          } else if ((uint32_t)w == 1u) {
+            acc = __fadd_rn(g, acc);
+          } else {
+            act = false;
+          }
+        } else {
+          __hip_atomic_store(&a.acc[v], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          stores_done();
+          w = __hip_atomic_fetch_add(&a.word[p], 1ull << 32, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+          asm volatile("" ::: "memory");  // nothing below is read before the count
+          if ((uint32_t)(w >> 32) + 1u == (uint32_t)w) many = true;
+          else act = false;
+          acc = g;
+        }
+        v = p;
+      }
+    }
+    unsigned long long left = __ballot(many);
+    if (left) {
+      int32_t k0 = 0, k1 = 0, sb = 0, root = -1;
+      const int32_t *dst = nullptr;
+      if (many) {
+        int32_t lo = 0, hi = a.num_inst;  // insts[lo].sbase <= v < insts[hi].sbase
+        while (hi - lo > 1) {
+          const int32_t mid = (lo + hi) >> 1;
+          if (a.insts[mid].sbase <= v) lo = mid;
+          else hi = mid;
+        }
+        const InstDev id = a.insts[lo];
+        const GraphDev &G = a.graphs[id.graph];
         sb = id.sbase;
         root = id.source;
-        G = &a.graphs[id.graph];
-        vx = x - sb;
-        k0 = G->u_out_off[vx];
-        k1 = G->u_out_off[vx + 1];
-        // four out-edges at a time: their heads, then the heads' parent
-        // entries, each step's loads issued together (past the list's end a
-        // lane reads edge kb again and its test fails)
-        for (int32_t kb = k0; kb < k1; kb += 4) {
-          int32_t c[4], pr[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) c[q] = G->u_out_dst[kb + q < k1 ? kb + q : kb];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) pr[q] = a.pred[sb + c[q]];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if (kb + q < k1 && c[q] != root && pr[q] == kb + q) {
-              ++nch;
-              if (kb == k0) {
-                cm |= 1u << q;
-                cc[q] = c[q];
-              }
-            }
-          }
-        }
-      }
-      uint64_t tot;
-      const uint64_t ex = block_excl_scan64<BBS>((uint64_t)nch, scan, &tot);
-      if (tot > 0) {
-        if (tid == 0) sbase = atomicAdd(a.ctr, (unsigned int)tot);
-        __syncthreads();
-        uint32_t p = sbase + (uint32_t)ex;
-        if (idx < e && nch) {
-          if (k1 - k0 <= 4) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              if ((cm >> q) & 1u) {
-                a.lv_v[p] = sb + cc[q];
-                a.lv_i[p] = ins;
-                ++p;
-              }
-            }
-          } else {
-            for (int32_t k = k0; k < k1; ++k) {
-              const int32_t c = G->u_out_dst[k];
-              if (c != root && a.pred[sb + c] == k) {
-                a.lv_v[p] = sb + c;
-                a.lv_i[p] = ins;
-                ++p;
-              }
-            }
-          }
-        }
-        __syncthreads();
-      }
-    }
-    grid_barrier(a.flags, a.go, epoch);
-    s = e;
-    e = (int)__hip_atomic_load(a.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    ++L;
-    if (bid == 0 && tid == 0) a.lv_off[L + 1] = e;
-  }
-  // levels 0..L-1 are non-empty; lv_off[0..L] are their bounds
-  grid_barrier(a.flags, a.go, epoch);
-  // ---- bottom-up: deepest level first
-  for (int lv = L - 1; lv >= 0; --lv) {
-    const int ls = a.lv_off[lv], le = a.lv_off[lv + 1];
-    for (int idx = ls + bid * BBS + tid; idx < le; idx += nb * BBS) {
-      const int32_t y = a.lv_v[idx];
-      const InstDev id = a.insts[a.lv_i[idx]];
-      const GraphDev &G = a.graphs[id.graph];
-      const int32_t sb = id.sbase, vy = y - sb;
-      float acc = a.gcost[y];
-      const int32_t k0 = G.u_out_off[vy], k1 = G.u_out_off[vy + 1];
-      // as in the top-down pass, four out-edges at a time; a head's subtree
-      // sum loads with its parent entry and counts only for a child (in
-      // edge order)
-      for (int32_t kb = k0; kb < k1; kb += 4) {
-        int32_t lc[4], pr[4];
-        float av[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) lc[q] = G.u_out_dst[kb + q < k1 ? kb + q : kb];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          pr[q] = a.pred[sb + lc[q]];
-          av[q] = a.acc[sb + lc[q]];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (kb + q < k1 && lc[q] != id.source && pr[q] == kb + q) acc = __fadd_rn(acc, av[q]);
-      }
-      a.acc[y] = acc;
-    }
-    grid_barrier(a.flags, a.go, epoch);
-  }
-  if (bid == 0 && tid == 0) *a.nlevels = L;
-}
-
-// The same two passes with each instance's tree in a workgroup of its own
-// (blocks loop over the instances) and block barriers only: for deep trees
-// (grids, meshes), whose levels are many and small.  Instance i's level
-// list occupies lv_v[sbase_i, sbase_i + n_i) and the ends of its levels
-// lv_i[sbase_i + l] (a tree has at most n_i levels).  The top-down pass
-// appends each entry's children together, in edge order, and entries'
-// children in list order, so the children of the entry at position p are
-// the list positions [lv_cs[p], lv_cs[p + 1]) (the list's end for the last
-// entry); the bottom-up pass sums them from lv_acc, the subtree sums by
-// list position, in that order (edge order, as the grid-wide pass does).
-// The top-down step also keeps the level it builds in LDS (the first
-// kLevelLds entries, double-buffered by level parity), so the next step reads
-// its entries there instead of from the global list it has just written.
-constexpr int kLevelLds = 4096;
-
-__global__ __launch_bounds__(BBS) void bw_wg_kernel(BackArgs a) {
-  __shared__ uint64_t scan[BBS / SSSP_WAVE + 1];
-  __shared__ int32_t cnt;
-  __shared__ int32_t lvl[2][kLevelLds];
-  const int tid = threadIdx.x;
-  int lmax = 0;
-  for (int ins = blockIdx.x; ins < a.num_inst; ins += gridDim.x) {
-    const InstDev id = a.insts[ins];
-    const GraphDev G = a.graphs[id.graph];  // by value: its fields stay in registers
-    const int32_t sb = id.sbase;
-    int32_t *V = a.lv_v + sb, *LE = a.lv_i + sb, *CS = a.lv_cs + sb;
-    float *AL = a.lv_acc + sb;
-    if (tid == 0) {
-      V[0] = id.source;  // graph-local ids in this path
-      lvl[0][0] = id.source;
-      cnt = 1;
-    }
-    __syncthreads();
-    // ---- top-down: level L occupies [s, e) of V, and its first kLevelLds
-    // entries lvl[L & 1]
-    int s = 0, e = 1, L = 0;
-    while (s < e) {
-      const int32_t *cur = lvl[L & 1];
-      int32_t *nxt = lvl[(L & 1) ^ 1];
-      for (int b0 = s; b0 < e; b0 += BBS) {
-        const int idx = b0 + tid;
-        int32_t k0 = 0, k1 = 0;
-        uint32_t nch = 0;
-        // the children among the first four out-edges (bit q: edge k0 + q)
-        uint32_t cm = 0;
-        int32_t cc[4] = {0, 0, 0, 0};
-        if (idx < e) {
-          const int32_t x = idx - s < kLevelLds ? cur[idx - s] : V[idx];
-          k0 = G.u_out_off[x];
-          k1 = G.u_out_off[x + 1];
-          // four out-edges at a time: their heads, then the heads' parent
-          // entries, each step's loads issued together (past the list's
-          // end a lane reads edge kb again and its test fails)
+        dst = G.u_out_dst;
+        k0 = G.u_out_off[v - sb];
+        k1 = G.u_out_off[v - sb + 1];
+        if (k1 - k0 <= kBackScan) {
+          // four out-edges at a time, each step's loads issued together
+          // (past the list's end a lane reads edge kb again and its test
+          // fails)
           for (int32_t kb = k0; kb < k1; kb += 4) {
             int32_t c[4], pr[4];
+            float av[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) c[q] = G.u_out_dst[kb + q < k1 ? kb + q : kb];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) pr[q] = a.pred[sb + c[q]];
+            for (int q = 0; q < 4; ++q) c[q] = dst[kb + q < k1 ? kb + q : kb];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              if (kb + q < k1 && c[q] != id.source && pr[q] == kb + q) {
-                ++nch;
-                if (kb == k0) {
-                  cm |= 1u << q;
-                  cc[q] = c[q];
-                }
-              }
+              pr[q] = a.pred[sb + c[q]];
+              av[q] = __hip_atomic_load(&a.acc[sb + c[q]], __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
             }
-          }
-        }
-        uint64_t tot;
-        const uint64_t ex = block_excl_scan64<BBS>((uint64_t)nch, scan, &tot);
-        if (idx < e) CS[idx] = cnt + (int32_t)ex;  // (cnt is current: the scan's barriers)
-        if (tot > 0) {
-          uint32_t p = (uint32_t)cnt + (uint32_t)ex;
-          if (idx < e && nch) {
-            // the next level starts at e: entry p is its entry p - e
-            if (k1 - k0 <= 4) {
 #pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                if ((cm >> q) & 1u) {
-                  V[p] = cc[q];
-                  if (p - (uint32_t)e < (uint32_t)kLevelLds) nxt[p - e] = cc[q];
-                  ++p;
-                }
-              }
-            } else {
-              for (int32_t k = k0; k < k1; ++k) {
-                const int32_t c = G.u_out_dst[k];
-                if (c != id.source && a.pred[sb + c] == k) {
-                  V[p] = c;
-                  if (p - (uint32_t)e < (uint32_t)kLevelLds) nxt[p - e] = c;
-                  ++p;
-                }
-              }
-            }
+            for (int q = 0; q < 4; ++q)
+              if (kb + q < k1 && c[q] != root && pr[q] == kb + q) acc = __fadd_rn(acc, av[q]);
           }
-          __syncthreads();
-          if (tid == 0) cnt += (int32_t)tot;
-          __syncthreads();
+          many = false;
         }
       }
-      if (tid == 0) LE[L] = e;
-      ++L;
-      s = e;
-      e = cnt;  // every thread reads it after the barriers above
-      __syncthreads();
-    }
-    lmax = L > lmax ? L : lmax;
-    // ---- bottom-up: deepest level first; an entry's children are the
-    // list range its top-down step recorded, summed in list (edge) order
-    const int nv = e;  // the tree's size: the list's end
-    for (int lv = L - 1; lv >= 0; --lv) {
-      const int ls = lv == 0 ? 0 : LE[lv - 1], le = LE[lv];
-      for (int idx = ls + tid; idx < le; idx += BBS) {
-        const int32_t y = V[idx];
-        const int32_t c0 = CS[idx], c1 = idx + 1 < nv ? CS[idx + 1] : nv;
-        float acc = a.gcost[sb + y];
-        for (int32_t p = c0; p < c1; ++p) acc = __fadd_rn(acc, AL[p]);
-        AL[idx] = acc;
-        a.acc[sb + y] = acc;
+      left = __ballot(many);
+      while (left) {
+        const int o = __ffsll(left) - 1;
+        left &= left - 1;
+        const int32_t ob = __shfl(k0, o), oe = __shfl(k1, o), osb = __shfl(sb, o);
+        const int32_t ort = __shfl(root, o);
+        const int32_t *od = (const int32_t *)(((unsigned long long)(uint32_t)__shfl(
+                                                   (int)((unsigned long long)dst >> 32), o)
+                                               << 32) |
+                                              (uint32_t)__shfl((int)(unsigned long long)dst, o));
+        float s = __shfl(acc, o);
+        int32_t c = ob + l < oe ? od[ob + l] : -1;
+        for (int32_t kb = ob; kb < oe; kb += SSSP_WAVE) {
+          const int32_t cn = kb + SSSP_WAVE + l < oe ? od[kb + SSSP_WAVE + l] : -1;
+          bool ch = false;
+          float av = 0.0f;
+          if (c >= 0) {
+            ch = c != ort && a.pred[osb + c] == kb + l;
+            if (ch)
+              av = __hip_atomic_load(&a.acc[osb + c], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+          }
+          unsigned long long cm = __ballot(ch);
+          while (cm) {
+            const int q = __ffsll(cm) - 1;
+            cm &= cm - 1;
+            s = __fadd_rn(s, __uint_as_float((uint32_t)__builtin_amdgcn_readlane(
+                                 (int)__float_as_uint(av), q)));
+          }
+          c = cn;
+        }
+        if (l == o) acc = s;
       }
-      __syncthreads();
     }
   }
-  if (tid == 0 && lmax) atomicMax(a.nlevels, lmax);
+  // (no barrier: a wave on a long path would hold the block's other waves)
+  steps = (int32_t)wave_sum64(steps);
+  if (l == 0 && steps)
+    atomicAdd(&a.ctl[(1 + (i >> 6) % kBackSums) * kBackStride], (unsigned int)steps);
+}
+
+// Only for a pred array with stray trees or parent cycles (the walk does not
+// reach every vertex): each vertex's parent moves up to its parent's parent
+// until it is one of the three ends or, after log2(n) rounds, still on a
+// cycle; the sums of vertices that do not end under the root are cleared.
+__global__ __launch_bounds__(1024) void bw_prune_kernel(BackArgs a) {
+  int32_t reached = 0;
+  for (int q = lane_id(); q < kBackSums; q += SSSP_WAVE)
+    reached += (int32_t)a.ctl[(1 + q) * kBackStride];
+  if (a.ctl[0] == 0u && wave_sum64(reached) == a.total) return;
+  for (int32_t ins = blockIdx.x; ins < a.num_inst; ins += gridDim.x) {
+    const InstDev id = a.insts[ins];
+    for (int64_t far = 1; far < 2 * (int64_t)id.n; far <<= 1) {
+      for (int32_t x = (int32_t)threadIdx.x; x < id.n; x += 1024) {
+        int32_t *at = &a.par[id.sbase + x];
+        const int32_t up = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (up >= 0)
+          __hip_atomic_store(at,
+                             __hip_atomic_load(&a.par[up], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      stores_done();
+      __syncthreads();
+    }
+    for (int32_t x = (int32_t)threadIdx.x; x < id.n; x += 1024)
+      if (__hip_atomic_load(&a.par[id.sbase + x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) !=
+          kUnderRoot)
+        a.acc[id.sbase + x] = 0.0f;
+  }
 }
 
 // grad_w[ebase[g] + e] = sum over instances i of graph g (instance order) of
-// acc_i[head(e)] if pred_i[head(e)] == e
-__global__ void bw_grad_kernel(BackArgs a, const int32_t *goff, const int32_t *ginst,
-                               const int32_t *ebase, int32_t num_graphs, int32_t total_m,
-                               float *grad_w) {
-  for (int32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < total_m;
-       q += gridDim.x * blockDim.x) {
-    int lo = 0, hi = num_graphs;  // ebase[lo] <= q < ebase[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (ebase[mid] <= q) lo = mid;
-      else hi = mid;
+// acc_i[head(e)] if pred_i[head(e)] == e: a thread per vertex, whose entries
+// are read once, coalesced, and added to the sums of its in-edges in
+// registers; past kBackIn in-edges the thread, which alone touches them, adds
+// in memory.
+__global__ __launch_bounds__(BBS) void bw_grad_kernel(BackArgs a) {
+  for (int32_t b = blockIdx.x; b < a.blocks; b += gridDim.x) {
+    const int32_t g = block_graph(a, b);
+    const GraphDev &G = a.graphs[g];
+    const int32_t y = (b - a.bbase[g]) * BBS + (int32_t)threadIdx.x;
+    if (y >= G.n) continue;
+    InEdges in;
+    in.load(G, y, false);
+    float *grad = a.grad_w + a.ebase[g];
+    float sum[kBackIn];
+#pragma unroll
+    for (int q = 0; q < kBackIn; ++q) sum[q] = 0.0f;
+    const int32_t j1 = a.goff[g + 1];
+#pragma unroll 4
+    for (int32_t j = a.goff[g]; j < j1; ++j) {
+      const InstDev id = a.insts[a.ginst[j]];
+      const int32_t e = a.pred[id.sbase + y];
+      const float v = a.acc[id.sbase + y];
+      if (e < 0 || y == id.source) continue;
+      if (in.deg <= kBackIn) {
+#pragma unroll
+        for (int q = 0; q < kBackIn; ++q) sum[q] = in.eid[q] == e ? __fadd_rn(sum[q], v) : sum[q];
+      } else if (e < G.m && G.u_out_dst[e] == y) {
+        grad[e] = __fadd_rn(grad[e], v);
+      }
     }
-    const GraphDev &G = a.graphs[lo];
-    const int32_t e = q - ebase[lo];
-    const int32_t y = G.u_out_dst[e];
-    float sum = 0.0f;
-    for (int32_t j = goff[lo]; j < goff[lo + 1]; ++j) {
-      const InstDev id = a.insts[ginst[j]];
-      if (y != id.source && a.pred[id.sbase + y] == e) sum = __fadd_rn(sum, a.acc[id.sbase + y]);
+    if (in.deg <= kBackIn) {
+#pragma unroll
+      for (int q = 0; q < kBackIn; ++q)
+        if (q < in.deg) grad[in.eid[q]] = sum[q];
     }
-    grad_w[q] = sum;
   }
 }
 
-hipError_t launch_backward(const BackArgs &a, const LaunchGeom &geo, const int32_t *goff,
-                           const int32_t *ginst, const int32_t *ebase, int32_t num_graphs,
-                           int32_t total_m, float *grad_w, hipStream_t stream) {
-  hipError_t e;
-  {
-    int zb = (a.total + 255) / 256;
-    if (zb > 4096) zb = 4096;
-    hipLaunchKernelGGL(bw_zero_kernel, dim3(zb < 1 ? 1 : zb), dim3(256), 0, stream, a);
-  }
-  hipLaunchKernelGGL(bw_init_kernel, dim3(1), dim3(256), 0, stream, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (geo.wg) {
-    int nbk = a.num_inst < geo.blocks ? a.num_inst : geo.blocks;
-    if (nbk < 1) nbk = 1;
-    hipLaunchKernelGGL(bw_wg_kernel, dim3(nbk), dim3(BBS), 0, stream, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  } else {
-    int occ = 0;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)bw_levels_kernel,
-                                                          BBS, 0)) != hipSuccess)
-      return e;
-    int per_cu = geo.blocks / (geo.cus > 0 ? geo.cus : 1);
-    if (occ < per_cu) per_cu = occ;
-    if (per_cu < 1) return hipErrorLaunchFailure;
-    BackArgs arg = a;
-    void *params[] = {&arg};
-    e = hipLaunchCooperativeKernel((const void *)bw_levels_kernel, dim3(geo.cus * per_cu),
-                                   dim3(BBS), params, 0, stream);
-    if (e != hipSuccess) return e;
-  }
-  int blocks = (total_m + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(bw_grad_kernel, dim3(blocks), dim3(256), 0, stream, a, goff, ginst, ebase,
-                     num_graphs, total_m, grad_w);
+hipError_t launch_backward(const BackArgs &a, int32_t max_inst, hipStream_t stream) {
+  const auto grid = [](int64_t items, int64_t most) {
+    const int64_t b = (items + BBS - 1) / BBS;
+    return dim3((unsigned int)(b < 1 ? 1 : b > most ? most : b));
+  };
+  const int64_t z = a.total > a.total_m ? a.total : a.total_m;
+  hipLaunchKernelGGL(bw_zero_kernel, grid(z, 8192), dim3(BBS), 0, stream, a);
+  dim3 vg((unsigned int)(a.blocks < 65536 ? a.blocks : 65536));
+  const int chunks = (max_inst + kBackChunk - 1) / kBackChunk;
+  dim3 pg(vg.x, (unsigned int)(chunks < 64 ? chunks : 64));
+  hipLaunchKernelGGL(bw_parent_kernel, pg, dim3(BBS), 0, stream, a);
+  hipLaunchKernelGGL(bw_walk_kernel, grid(a.total, INT_MAX), dim3(BBS), 0, stream, a);
+  hipLaunchKernelGGL(bw_prune_kernel, dim3((unsigned int)(a.num_inst < 256 ? a.num_inst : 256)),
+                     dim3(1024), 0, stream, a);
+  hipLaunchKernelGGL(bw_grad_kernel, vg, dim3(BBS), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -11,7 +11,9 @@ namespace sssp {
 // Threads per block of the persistent round kernel: one block per CU (16
 // waves) keeps the grid barrier at 256 participants while filling the CU.
 constexpr int kRoundBlock = 1024;
-constexpr int kBackBlock = 512;   // threads per block of the backward kernels
+constexpr int kBackBlock = 256;   // threads per block of the backward kernels
+constexpr int kBackStride = 32;   // words between its counters
+constexpr int kBackCtl = 65 * kBackStride;
 constexpr int kMaxBlocks = 4096;  // upper bound on a persistent grid
 
 // Per-block partial minima of a single solve, [kParts][kMaxBlocks]: every
@@ -321,24 +323,20 @@ hipError_t launch_permute_edges(const int32_t *perm, int64_t m, const int32_t *i
 struct BackArgs {
   const GraphDev *graphs;
   const InstDev *insts;
-  int32_t num_inst;
-  int32_t total;
+  const int32_t *goff, *ginst;  // graph g's instances: ginst[goff[g]] .. ginst[goff[g + 1] - 1]
+  const int32_t *ebase;         // graph g's edges in grad_w start here
+  const int32_t *bbase;         // and its blocks in the per-vertex passes (kBackBlock vertices each)
+  int32_t num_graphs, num_inst, blocks;
+  int32_t total, total_m;
   const int32_t *pred;
   const float *gcost;
-  float *acc;
-  int32_t *lv_v, *lv_i;       // level lists (vertex state index, instance)
-  // one-workgroup path, per list position: where the entry's children start
-  // in the list, and the entry's subtree sum
-  int32_t *lv_cs;
-  float *lv_acc;
-  int32_t *lv_off;            // level offsets, capacity total + 2
-  int32_t *nlevels;           // device scalar: number of non-empty levels
-  unsigned int *flags;        // grid barrier flags, kMaxBlocks * kFlagStride
-  unsigned int *go;           // grid barrier release word
-  unsigned int *ctr;          // append counter for the level being built
+  float *grad_w;
+  float *acc;                   // [total] subtree sums
+  int32_t *par;                 // [total] the parent's entry, or a negative end
+  unsigned long long *word;     // [total] children, arrivals or the first of two children
+  unsigned int *ctl;            // [kBackCtl]
 };
-hipError_t launch_backward(const BackArgs &a, const LaunchGeom &geo, const int32_t *ginst_off,
-                           const int32_t *ginst, const int32_t *ebase, int32_t num_graphs,
-                           int32_t total_m, float *grad_w, hipStream_t stream);
+// max_inst: the most instances of one graph
+hipError_t launch_backward(const BackArgs &a, int32_t max_inst, hipStream_t stream);
 
 }  // namespace sssp
