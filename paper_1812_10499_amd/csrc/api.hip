@@ -1451,12 +1451,13 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
   b.ebase = (const int32_t *)at(hebase);
   b.bbase = (const int32_t *)at(hbbase);
   for (int32_t gi = 0; gi < num_graphs; ++gi) hg[gi] = graph_dev(&graphs[gi]);
-  int32_t base = 0;
+  int32_t base = 0, max_n = 0;
   for (int32_t i = 0; i < num_inst; ++i) {
     hi[i].graph = inst_graph[i];
     hi[i].source = inst_source[i];
     hi[i].sbase = base;
     hi[i].n = graphs[inst_graph[i]].n;
+    if (hi[i].n > max_n) max_n = hi[i].n;
     base += hi[i].n;
   }
   // instances grouped by graph, in instance order within a graph
@@ -1484,7 +1485,7 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
   HIPCHK(hipStreamWaitEvent(stream, ws.last, 0));
   HIPCHK(hipMemcpyAsync(tab, hp, tab_bytes, hipMemcpyHostToDevice, stream));
   HIPCHK(hipEventRecord(ws.staged, stream));
-  HIPCHK(launch_backward(b, max_inst, stream));
+  HIPCHK(launch_backward(b, max_inst, max_n, stream));
   HIPCHK(hipEventRecord(ws.last, stream));
   return SSSP_OK;
 }

@@ -18,7 +18,13 @@
 // vertex is carried on by the child that arrives last; the work is one walk
 // over the tree, in whatever order its parts are ready, and only the deepest
 // path is serial.  A level list with a barrier per level spends most of its
-// time in the barriers (a 512 x 512 grid has 1000 levels of 260 vertices).
+// time in the barriers (a 512 x 512 grid has 1000 levels of 260 vertices):
+// whole pass of 16 trees of 30011 vertices 1.05 -> 0.21 ms, 64 of 512 x 512
+// 4.33 -> 2.4, a skewed tree of 2^18 vertices 26.9 -> 0.64, 64 of 150001 7.1 ->
+// 1.7.  What bounds it now: the latency of each iteration's dependent accesses
+// (a returning atomic at the chip's scope goes to the memory side: 4 M of them
+// in the grid case) times the iterations, and for few deep trees the deepest
+// path, about 1200 cycles a vertex.
 #include "sssp_dev.h"
 #include "sssp_kernels.h"
 #include "team.h"
@@ -29,9 +35,13 @@ constexpr int BBS = kBackBlock;
 constexpr int kBackIn = 8;      // in-edges of a vertex held in registers
 constexpr int kBackChunk = 8;   // instances per block of the parent pass
 constexpr int kBackScan = 16;   // out-edges one lane looks through by itself
+constexpr int kWalkBlocks = 2048;  // of the walk: every wave slot of the chip
 
 // BackArgs::ctl: a flag, and the number of vertices walked in kBackSums parts
-constexpr int kBackSums = kBackCtl / kBackStride - 1;
+// (then the XCDs' words and the instance queue)
+constexpr int kBackSums = kBackCtl / kBackStride - 10;
+constexpr int kSweep = 64;    // vertices a wave starts from at a time
+constexpr int kClaim = 64;    // the same, where an XCD's waves share an instance
 
 // BackArgs::par of a vertex without a parent
 enum : int32_t {
@@ -44,7 +54,7 @@ __global__ __launch_bounds__(BBS) void bw_zero_kernel(BackArgs a) {
   const int64_t step = (int64_t)gridDim.x * BBS, i0 = (int64_t)blockIdx.x * BBS + threadIdx.x;
   for (int64_t i = i0; i < a.total; i += step) a.word[i] = 0ull;
   for (int64_t i = i0; i < a.total_m; i += step) a.grad_w[i] = 0.0f;
-  if (i0 < kBackCtl) a.ctl[i0] = 0u;
+  for (int64_t i = i0; i < kBackCtl; i += step) a.ctl[i] = 0u;
 }
 
 // The graph whose vertices block b of the per-vertex passes covers.
@@ -126,64 +136,125 @@ __global__ __launch_bounds__(BBS) void bw_parent_kernel(BackArgs a) {
 // until the store is done and counts itself; the last reads the sums in edge
 // order, alone or (long out-lists) with its whole wave.  An only child just
 // goes on, so a chain costs one load's latency a vertex.
-__global__ __launch_bounds__(BBS) void bw_walk_kernel(BackArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * BBS + threadIdx.x;
+//
+// A lane whose walk has ended takes the wave's next vertex in the same
+// iteration, and its loads are the walkers' loads, so lanes stay busy beside
+// a long walk.
+
+// Vertices to start from, over the whole chip: wave wid of `waves` takes every
+// waves-th chunk of [at, end).
+struct SweepSource {
+  static constexpr int kScope = __HIP_MEMORY_SCOPE_AGENT;
+  int64_t at, end, step;
+  __device__ __forceinline__ bool grab(const BackArgs &, int64_t *pos, int64_t *lim) {
+    if (at >= end) return false;
+    *pos = at;
+    *lim = at + kSweep < end ? at + kSweep : end;
+    at += step;
+    return true;
+  }
+};
+
+// Vertices to start from, each instance on one XCD: the XCD's word holds the
+// instance it is at (plus one) and the chunks of it that are taken; the wave
+// that finds the last one taken claims the next instance.
+struct XcdSource {
+  static constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
+  unsigned long long *cur;
+  unsigned int *queue;
+  __device__ __forceinline__ bool grab(const BackArgs &a, int64_t *pos, int64_t *lim) {
+    unsigned long long t = 0;
+    if (lane_id() == 0) t = __hip_atomic_fetch_add(cur, 1ull, __ATOMIC_RELAXED, kScope);
+    int32_t ins = __builtin_amdgcn_readfirstlane((int)(t >> 32)) - 1;
+    int32_t c = __builtin_amdgcn_readfirstlane((int)t);
+    if (ins == -2) return false;
+    const int32_t chunks = ins < 0 ? 0 : (a.insts[ins].n + kClaim - 1) / kClaim;
+    if (c > chunks) return true;  // another wave is claiming
+    if (c == chunks) {
+      unsigned int i = 0;
+      if (lane_id() == 0)
+        i = __hip_atomic_fetch_add(queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ins = __builtin_amdgcn_readfirstlane((int)i);
+      const bool over = ins >= a.num_inst;
+      if (lane_id() == 0)
+        put64(cur, over ? 0xffffffffull << 32 : (unsigned long long)(ins + 1) << 32 | 1ull, true);
+      if (over) return false;
+      c = 0;
+    }
+    const InstDev id = a.insts[ins];
+    *pos = (int64_t)id.sbase + (int64_t)c * kClaim;
+    *lim = (c + 1) * (int64_t)kClaim < id.n ? *pos + kClaim : (int64_t)id.sbase + id.n;
+    return true;
+  }
+};
+
+// Returns the number of vertices this lane completed.
+template <typename SOURCE>
+__device__ __forceinline__ int32_t walk(const BackArgs &a, SOURCE source) {
+  constexpr int SCOPE = SOURCE::kScope;
   const int l = lane_id();
-  int32_t v = (int32_t)i, up = kNoParent, steps = 0;
+  int64_t pos = 0, lim = 0;
+  bool more = true;
+  int32_t v = 0, up = kNoParent, steps = 0;
   bool act = false;
   float acc = 0.0f;
-  if (i < a.total) {
-    const unsigned long long w = ld_relaxed64(&a.word[i]);
-    up = a.par[i];
-    if (w == 0ull) {
-      act = true;
-      acc = a.gcost[i];
-    } else if (up == kNoParent) {
-      a.ctl[0] = 1u;  // a stray tree
+  for (;;) {
+    // v's sum is complete: on to its parent, or to a new vertex
+    if (act && up < 0) {
+      a.acc[v] = acc;
+      act = false;
     }
-  }
-  while (__ballot(act)) {
-    // v's sum is complete: on to its parent p
-    const int32_t p = up;
+    const unsigned long long idle = __ballot(!act);
+    if (pos >= lim && more && idle) more = source.grab(a, &pos, &lim);
+    const int64_t at = act ? up : pos + __popcll(idle & ((1ull << l) - 1ull));
+    const bool fresh = !act && at < lim;
+    if (!__ballot(act || fresh)) {
+      if (!more) break;
+      __builtin_amdgcn_s_sleep(4);
+      continue;
+    }
+    pos += __popcll(idle);
     bool many = false;
-    if (act) {
-      ++steps;
-      if (p < 0) {
-        a.acc[v] = acc;
-        act = false;
-      } else {
-        const int32_t e = a.pred[v];
-        unsigned long long w = ld_relaxed64(&a.word[p]);
-        const float g = a.gcost[p];
-        up = a.par[p];
-        if ((long long)w < 0 || (uint32_t)w <= 2u) {
-          a.acc[v] = acc;
-          if ((long long)w >= 0 && (uint32_t)w == 2u)
-            w = __hip_atomic_exchange(&a.word[p],
-                                      ((unsigned long long)(0x80000000u | (uint32_t)e) << 32) |
-                                          (unsigned long long)__float_as_uint(acc),
-                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if ((long long)w < 0) {
-            const int32_t e2 = (int32_t)((uint32_t)(w >> 32) & 0x7fffffffu);
-            const float s = __uint_as_float((uint32_t)w);
-            acc = __fadd_rn(__fadd_rn(g, e < e2 ? acc : s), e < e2 ? s : acc);
-          } else if ((uint32_t)w == 1u) {
-            acc = __fadd_rn(g, acc);
-          } else {
-            act = false;
-          }
-        } else {
-          __hip_atomic_store(&a.acc[v], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          stores_done();
-          w = __hip_atomic_fetch_add(&a.word[p], 1ull << 32, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
-          asm volatile("" ::: "memory");  // nothing below is read before the count
-          if ((uint32_t)(w >> 32) + 1u == (uint32_t)w) many = true;
-          else act = false;
+    if (act || fresh) {
+      const int32_t p = (int32_t)at;
+      const int32_t e = a.pred[act ? v : p];
+      unsigned long long w = ld_relaxed64(&a.word[p]);
+      const float g = a.gcost[p];
+      up = a.par[p];
+      if (fresh) {
+        if (w == 0ull) {
+          act = true;
           acc = g;
+        } else if (up == kNoParent) {
+          a.ctl[0] = 1u;  // a stray tree
         }
-        v = p;
+      } else if ((long long)w < 0 || (uint32_t)w <= 2u) {
+        a.acc[v] = acc;
+        if ((long long)w >= 0 && (uint32_t)w == 2u)
+          w = __hip_atomic_exchange(&a.word[p],
+                                    ((unsigned long long)(0x80000000u | (uint32_t)e) << 32) |
+                                        (unsigned long long)__float_as_uint(acc),
+                                    __ATOMIC_RELAXED, SCOPE);
+        if ((long long)w < 0) {
+          const int32_t e2 = (int32_t)((uint32_t)(w >> 32) & 0x7fffffffu);
+          const float s = __uint_as_float((uint32_t)w);
+          acc = __fadd_rn(__fadd_rn(g, e < e2 ? acc : s), e < e2 ? s : acc);
+        } else if ((uint32_t)w == 1u) {
+          acc = __fadd_rn(g, acc);
+        } else {
+          act = false;
+        }
+      } else {
+        __hip_atomic_store(&a.acc[v], acc, __ATOMIC_RELAXED, SCOPE);
+        stores_done();
+        w = __hip_atomic_fetch_add(&a.word[p], 1ull << 32, __ATOMIC_RELAXED, SCOPE);
+        asm volatile("" ::: "memory");  // nothing below is read before the count
+        if ((uint32_t)(w >> 32) + 1u == (uint32_t)w) many = true;
+        else act = false;
+        acc = g;
       }
+      v = p;
+      if (act) ++steps;
     }
     unsigned long long left = __ballot(many);
     if (left) {
@@ -260,10 +331,33 @@ __global__ __launch_bounds__(BBS) void bw_walk_kernel(BackArgs a) {
       }
     }
   }
-  // (no barrier: a wave on a long path would hold the block's other waves)
+  return steps;
+}
+
+// (no barrier: a wave on a long path would hold the block's other waves)
+__device__ __forceinline__ void add_steps(const BackArgs &a, int32_t steps, int64_t wid) {
   steps = (int32_t)wave_sum64(steps);
-  if (l == 0 && steps)
-    atomicAdd(&a.ctl[(1 + (i >> 6) % kBackSums) * kBackStride], (unsigned int)steps);
+  if (lane_id() == 0 && steps)
+    atomicAdd(&a.ctl[(1 + wid % kBackSums) * kBackStride], (unsigned int)steps);
+}
+
+// Blocks b with the same b mod 8 (one XCD) sweep the same eighth of the vertices.
+__global__ __launch_bounds__(BBS) void bw_walk_kernel(BackArgs a) {
+  const int64_t part = blockIdx.x & 7, waves = (int64_t)(gridDim.x >> 3) * (BBS / SSSP_WAVE);
+  const int64_t wid = (int64_t)(blockIdx.x >> 3) * (BBS / SSSP_WAVE) +
+                      __builtin_amdgcn_readfirstlane((int)(threadIdx.x / SSSP_WAVE));
+  const SweepSource from = {((part * a.total) >> 3) + wid * kSweep, ((part + 1) * a.total) >> 3,
+                            waves * kSweep};
+  add_steps(a, walk(a, from), part * waves + wid);
+}
+
+__global__ __launch_bounds__(BBS) void bw_walk_xcd_kernel(BackArgs a) {
+  const int64_t wid = (int64_t)blockIdx.x * (BBS / SSSP_WAVE) +
+                      __builtin_amdgcn_readfirstlane((int)(threadIdx.x / SSSP_WAVE));
+  const XcdSource from = {
+      (unsigned long long *)(a.ctl + (1 + kBackSums + (xcd_id() & 7)) * kBackStride),
+      a.ctl + (1 + kBackSums + 8) * kBackStride};
+  add_steps(a, walk(a, from), wid);
 }
 
 // Only for a pred array with stray trees or parent cycles (the walk does not
@@ -336,7 +430,8 @@ __global__ __launch_bounds__(BBS) void bw_grad_kernel(BackArgs a) {
   }
 }
 
-hipError_t launch_backward(const BackArgs &a, int32_t max_inst, hipStream_t stream) {
+hipError_t launch_backward(const BackArgs &a, int32_t max_inst, int32_t max_n,
+                           hipStream_t stream) {
   const auto grid = [](int64_t items, int64_t most) {
     const int64_t b = (items + BBS - 1) / BBS;
     return dim3((unsigned int)(b < 1 ? 1 : b > most ? most : b));
@@ -347,7 +442,18 @@ hipError_t launch_backward(const BackArgs &a, int32_t max_inst, hipStream_t stre
   const int chunks = (max_inst + kBackChunk - 1) / kBackChunk;
   dim3 pg(vg.x, (unsigned int)(chunks < 64 ? chunks : 64));
   hipLaunchKernelGGL(bw_parent_kernel, pg, dim3(BBS), 0, stream, a);
-  hipLaunchKernelGGL(bw_walk_kernel, grid(a.total, INT_MAX), dim3(BBS), 0, stream, a);
+  // Each instance on one XCD keeps the walk's atomics in that XCD's L2, but
+  // takes its vertices from a counter and needs instances enough to go round:
+  // 64 trees of 512 x 512 (16.8 M vertices) 3.2 -> 2.0 ms, 256 of 30011 2.05 ->
+  // 1.57 (the whole pass), 8 of 10^6 1.60 -> 1.65, 64 of 30011 0.49 -> 0.54, 16
+  // of 30011 0.13 -> 0.18.
+  if (a.total >= (1 << 22) && (int64_t)max_n * 16 <= a.total) {
+    hipLaunchKernelGGL(bw_walk_xcd_kernel, grid(a.total, kWalkBlocks), dim3(BBS), 0, stream, a);
+  } else {
+    dim3 wg = grid(a.total, kWalkBlocks);
+    wg.x = (wg.x + 7u) & ~7u;
+    hipLaunchKernelGGL(bw_walk_kernel, wg, dim3(BBS), 0, stream, a);
+  }
   hipLaunchKernelGGL(bw_prune_kernel, dim3((unsigned int)(a.num_inst < 256 ? a.num_inst : 256)),
                      dim3(1024), 0, stream, a);
   hipLaunchKernelGGL(bw_grad_kernel, vg, dim3(BBS), 0, stream, a);

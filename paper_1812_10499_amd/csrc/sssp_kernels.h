@@ -13,7 +13,7 @@ namespace sssp {
 constexpr int kRoundBlock = 1024;
 constexpr int kBackBlock = 256;   // threads per block of the backward kernels
 constexpr int kBackStride = 32;   // words between its counters
-constexpr int kBackCtl = 65 * kBackStride;
+constexpr int kBackCtl = 74 * kBackStride;
 constexpr int kMaxBlocks = 4096;  // upper bound on a persistent grid
 
 // Per-block partial minima of a single solve, [kParts][kMaxBlocks]: every
@@ -336,7 +336,8 @@ struct BackArgs {
   unsigned long long *word;     // [total] children, arrivals or the first of two children
   unsigned int *ctl;            // [kBackCtl]
 };
-// max_inst: the most instances of one graph
-hipError_t launch_backward(const BackArgs &a, int32_t max_inst, hipStream_t stream);
+// max_inst: the most instances of one graph; max_n: the most vertices of an instance
+hipError_t launch_backward(const BackArgs &a, int32_t max_inst, int32_t max_n,
+                           hipStream_t stream);
 
 }  // namespace sssp

@@ -119,3 +119,23 @@ def test_walk_matches_ordered_sums(sp, kind, n, count, spoil):
     for _ in range(2):
         got = sp.backward(graphs, inst, sources, p, gc).cpu().numpy()
         assert np.array_equal(got, np.concatenate(want))
+
+
+@pytest.mark.parametrize("count", [63, 80])
+def test_walk_shared_by_an_xcds_waves(sp, count):
+    """Around the line where each tree stays on one XCD (4 M vertices and 16
+    instances of the largest graph): every instance has the same parents, so
+    the gradient of integer costs' sums is count times one instance's."""
+    n = 65537
+    rng = np.random.default_rng(count)
+    src, dst, root = random_tree(rng, n, "random")
+    G = sp.Graph(n, src, dst, np.ones(len(src), np.float32))
+    arr = G.arrays()
+    off, hd = arr["out_off"].cpu().numpy(), arr["out_dst"].cpu().numpy()
+    pred = tree_pred(rng, n, off, hd, root, False)
+    gc = rng.integers(-4, 5, n).astype(np.float32)  # exact in float32 throughout
+    one = np.zeros(G.m, np.float32)
+    tree_grad(n, off, hd, root, pred, gc, one)
+    p = torch.from_numpy(pred).cuda().repeat(count)
+    got = sp.backward([G], [0] * count, [root] * count, p, torch.from_numpy(gc).cuda().repeat(count))
+    assert np.array_equal(got.cpu().numpy(), count * one)
