@@ -402,7 +402,8 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
  * the speed of a solve: costs, parents and counters are the same under
  * every setting.  A zero field takes the default.
  *   blocks:      grid size, 1 .. the co-resident maximum (default: that
- *                maximum, one 1024-thread block per compute unit);
+ *                maximum, one 1024-thread block per compute unit, and half
+ *                of it for a single solve on at most 6291456 edges);
  *   solo_edges:  a phase with at most this many edges runs on one block
  *                with block barriers only (default 8192; negative: never);
  *   block_units: otherwise the phase runs on about (work units) /

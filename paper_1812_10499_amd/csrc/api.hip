@@ -170,6 +170,7 @@ sssp_status resolve_launch(DevWS &w, bool f32, bool batch, const sssp_launch *L,
     if (L->blocks < 1 || L->blocks > geo->blocks) return SSSP_ERR_ARG;
     geo->blocks = L->blocks;
   }
+  geo->all_blocks = !(L && L->blocks);
   a.solo_edges = env_flag("SSSP_SOLO_EDGES", 8192);
   if (L && L->solo_edges) a.solo_edges = L->solo_edges < 0 ? 0 : L->solo_edges;
   a.block_units = env_flag("SSSP_BLOCK_UNITS", 2048);

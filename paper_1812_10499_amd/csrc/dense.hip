@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void dense_init_kernel(RoundArgs a, DenseArgs 
     c->front_ctr[0] = c->front_ctr[1] = 0ull;
     c->open_ctr[0] = c->open_ctr[1] = 0ull;
     c->live_ctr[0] = c->live_ctr[1] = 0ull;
-    c->go = c->go_a = 0u;
+    c->go = 0u;
     c->deg_count = 0;
     c->solo_phases = 0;
     c->dead_deg = c->dead_deg_r = 0ull;

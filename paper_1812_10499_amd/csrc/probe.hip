@@ -159,12 +159,11 @@ __global__ __launch_bounds__(1024) void sync_k(int iters, int *out) {
 }
 
 // `iters` grid barriers of the round kernel (sssp::grid_barrier) over the
-// whole cooperative grid.  flags (kMaxBlocks * kFlagStride) and go must be
-// zero at launch.
-__global__ __launch_bounds__(1024) void grid_sync_k(unsigned int *flags, unsigned int *go,
-                                                    int iters) {
+// whole cooperative grid.  flags (kMaxBlocks * kFlagStride) must be zero at
+// launch.
+__global__ __launch_bounds__(1024) void grid_sync_k(unsigned int *flags, int iters) {
   unsigned int epoch = 0;
-  for (int i = 0; i < iters; ++i) sssp::grid_barrier(flags, go, epoch);
+  for (int i = 0; i < iters; ++i) sssp::grid_barrier(flags, epoch);
 }
 
 // One workgroup, 8 accesses per thread and iteration, all issued before
@@ -272,9 +271,8 @@ int probe_sync(int iters, int *out, void *stream) {
   return (int)hipGetLastError();
 }
 
-int probe_grid_sync(unsigned int *flags, unsigned int *go, int iters, int blocks,
-                    void *stream) {
-  void *args[] = {&flags, &go, &iters};
+int probe_grid_sync(unsigned int *flags, int iters, int blocks, void *stream) {
+  void *args[] = {&flags, &iters};
   return (int)hipLaunchCooperativeKernel((const void *)grid_sync_k, dim3(blocks), dim3(1024),
                                          args, 0, (hipStream_t)stream);
 }

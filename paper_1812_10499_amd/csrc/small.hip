@@ -416,7 +416,7 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
     ctl->front_ctr[0] = ctl->front_ctr[1] = 0ull;
     ctl->open_ctr[0] = ctl->open_ctr[1] = 0ull;
     ctl->live_ctr[0] = ctl->live_ctr[1] = 0ull;
-    ctl->go = ctl->go_a = 0u;
+    ctl->go = 0u;
     ctl->deg_count = nd;
     ctl->solo_phases = 0;
     ctl->dead_deg = ctl->dead_deg_r = 0ull;

@@ -67,7 +67,6 @@ struct Ctl {
   unsigned long long front_ctr[2];  // by round parity: (items << 32) | out-degree sum
   unsigned long long open_ctr[2];   // by round parity: (items << 32) | in-degree sum
   unsigned int go;                  // hand-over word: parked blocks wait on it
-  unsigned int go_a;                // barrier release word of the active blocks
   int32_t status;                   // 0, or an sssp_status code set on the device
   int32_t rounds;
   int32_t deg_count;    // pred: vertices queued for the equal-cost pass
@@ -165,6 +164,7 @@ constexpr int kMarks = 12;
 
 struct LaunchGeom {
   int blocks;  // persistent grid size (co-resident)
+  bool all_blocks = false;  // the caller left it at the default
   int cus;
   int small_n = 0;  // solves of at most this many vertices run in one workgroup each, state in LDS
   // scope OPEN only: 1: every instance in a workgroup of its own; 2: by a

@@ -48,7 +48,7 @@ def _lib():
                                             ctypes.c_uint32, vp]
     L.probe_chase.argtypes = [vp, vp, i64, vp, vp]
     L.probe_sync.argtypes = [ctypes.c_int, vp, vp]
-    L.probe_grid_sync.argtypes = [vp, vp, ctypes.c_int, ctypes.c_int, vp]
+    L.probe_grid_sync.argtypes = [vp, ctypes.c_int, ctypes.c_int, vp]
     L.probe_cu_access.argtypes = [ctypes.c_int, vp, ctypes.c_uint32, ctypes.c_int, vp, vp]
     return L
 
@@ -82,14 +82,13 @@ def grid_barrier_us(blocks: int, iters: int = 2000) -> float:
     microseconds."""
     import torch
     L = _lib()
-    flags = torch.zeros(4096 * 16 + 64, dtype=torch.int32, device="cuda")
+    flags = torch.zeros(4096 * 16, dtype=torch.int32, device="cuda")
     st = torch.cuda.current_stream().cuda_stream
     tot = 0.0
     for _ in range(3):
         flags.zero_()
-        tot += _time_ms(torch, lambda: L.probe_grid_sync(flags.data_ptr(),
-                                                         flags[4096 * 16:].data_ptr(), iters,
-                                                         blocks, st), reps=1)
+        tot += _time_ms(torch, lambda: L.probe_grid_sync(flags.data_ptr(), iters, blocks, st),
+                        reps=1)
     return tot / 3 * 1e3 / iters
 
 
