@@ -365,7 +365,7 @@ sssp_status sssp_solve_target(const sssp_csr *g, int32_t source, int32_t target,
                               sssp_stats *stats, void *stream);
 
 /*
- * Many independent solves in one persistent launch.
+ * Many independent solves in one launch of a rounds kernel.
  *   graphs[num_graphs] (host array of built graphs, all of one dtype)
  *   inst_graph[num_inst], inst_source[num_inst] (host): instance i solves
  *           graph inst_graph[i] from inst_source[i].

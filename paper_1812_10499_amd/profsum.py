@@ -30,9 +30,10 @@ from .build import kernel_source_hash
 
 def _short(name: str) -> str:
     name = name.replace(".kd", "")
-    for key in ("small_rounds_kernel", "wg_rounds_kernel", "bw_wg_kernel", "rounds_kernel",
-                "emit_kernel", "pred_degen_kernel", "init_fill_kernel",
-                "init_seed_kernel", "bw_levels_kernel", "bw_grad_kernel", "bw_init_kernel",
+    for key in ("small_rounds_kernel", "wg_rounds_kernel", "mesh_rounds_kernel",
+                "dense_rounds_kernel", "rounds_kernel", "emit_kernel", "pred_degen_kernel",
+                "init_fill_kernel", "init_seed_kernel", "bw_zero_kernel", "bw_parent_kernel",
+                "bw_walk_xcd_kernel", "bw_walk_kernel", "bw_prune_kernel", "bw_grad_kernel",
                 "bitwise_not"):
         if key in name:
             tmpl = ""
