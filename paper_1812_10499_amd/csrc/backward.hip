@@ -20,11 +20,11 @@
 // path is serial.  A level list with a barrier per level spends most of its
 // time in the barriers (a 512 x 512 grid has 1000 levels of 260 vertices):
 // whole pass of 16 trees of 30011 vertices 1.05 -> 0.21 ms, 64 of 512 x 512
-// 4.33 -> 2.4, a skewed tree of 2^18 vertices 26.9 -> 0.64, 64 of 150001 7.1 ->
-// 1.7.  What bounds it now: the latency of each iteration's dependent accesses
-// (a returning atomic at the chip's scope goes to the memory side: 4 M of them
-// in the grid case) times the iterations, and for few deep trees the deepest
-// path, about 1200 cycles a vertex.
+// 4.33 -> 2.3, a skewed tree of 2^18 vertices 26.9 -> 0.7, 64 of 150001 7.1 ->
+// 1.5.  What bounds it now: the latency of each iteration's dependent accesses
+// (returning atomics, performed on the memory side: 4 M in the grid case) times
+// the iterations, and for few deep trees the deepest path, about 1200 cycles a
+// vertex.
 #include "sssp_dev.h"
 #include "sssp_kernels.h"
 #include "team.h"
@@ -442,7 +442,7 @@ hipError_t launch_backward(const BackArgs &a, int32_t max_inst, int32_t max_n,
   const int chunks = (max_inst + kBackChunk - 1) / kBackChunk;
   dim3 pg(vg.x, (unsigned int)(chunks < 64 ? chunks : 64));
   hipLaunchKernelGGL(bw_parent_kernel, pg, dim3(BBS), 0, stream, a);
-  // Each instance on one XCD keeps the walk's atomics in that XCD's L2, but
+  // Each instance on one XCD keeps what its walkers read in that XCD's L2, but
   // takes its vertices from a counter and needs instances enough to go round:
   // 64 trees of 512 x 512 (16.8 M vertices) 3.2 -> 2.0 ms, 256 of 30011 2.05 ->
   // 1.57 (the whole pass), 8 of 10^6 1.60 -> 1.65, 64 of 30011 0.49 -> 0.54, 16
