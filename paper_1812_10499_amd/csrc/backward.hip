@@ -19,8 +19,8 @@
 // over the tree, in whatever order its parts are ready, and only the deepest
 // path is serial.  A level list with a barrier per level spends most of its
 // time in the barriers (a 512 x 512 grid has 1000 levels of 260 vertices):
-// whole pass of 16 trees of 30011 vertices 1.05 -> 0.21 ms, 64 of 512 x 512
-// 4.33 -> 2.3, a skewed tree of 2^18 vertices 26.9 -> 0.7, 64 of 150001 7.1 ->
+// whole pass of 16 trees of 30011 vertices 1.05 -> 0.20 ms, 64 of 512 x 512
+// 4.33 -> 2.1, a skewed tree of 2^18 vertices 26.9 -> 0.7, 64 of 150001 7.1 ->
 // 1.5.  What bounds it now: the latency of each iteration's dependent accesses
 // (returning atomics, performed on the memory side: 4 M in the grid case) times
 // the iterations, and for few deep trees the deepest path, about 1200 cycles a
@@ -33,7 +33,9 @@ namespace sssp {
 
 constexpr int BBS = kBackBlock;
 constexpr int kBackIn = 8;      // in-edges of a vertex held in registers
-constexpr int kBackChunk = 8;   // instances per block of the parent pass
+// instances per block of the parent pass (16 on 30011 vertices: 2, 4, 8 take 29,
+// 31, 38 us; 64 on 512 x 512: 181, 174, 174)
+constexpr int kBackChunk = 4;
 constexpr int kBackScan = 16;   // out-edges one lane looks through by itself
 constexpr int kWalkBlocks = 2048;  // of the walk: every wave slot of the chip
 
@@ -198,6 +200,11 @@ __device__ __forceinline__ int32_t walk(const BackArgs &a, SOURCE source) {
   int32_t v = 0, up = kNoParent, steps = 0;
   bool act = false;
   float acc = 0.0f;
+  // the instance of the lane's last scan of an out-list (looked up for every
+  // scan, the walk takes 2.0 against 1.8 ms on 64 trees of 512 x 512, 132
+  // against 118 us on 16 of 30011; out-lists read ahead of the count 1.9 and 125)
+  int32_t sb = 0, sn = 0, root = -1;
+  const int32_t *off = nullptr, *dst = nullptr;
   for (;;) {
     // v's sum is complete: on to its parent, or to a new vertex
     if (act && up < 0) {
@@ -258,22 +265,24 @@ __device__ __forceinline__ int32_t walk(const BackArgs &a, SOURCE source) {
     }
     unsigned long long left = __ballot(many);
     if (left) {
-      int32_t k0 = 0, k1 = 0, sb = 0, root = -1;
-      const int32_t *dst = nullptr;
+      int32_t k0 = 0, k1 = 0;
       if (many) {
-        int32_t lo = 0, hi = a.num_inst;  // insts[lo].sbase <= v < insts[hi].sbase
-        while (hi - lo > 1) {
-          const int32_t mid = (lo + hi) >> 1;
-          if (a.insts[mid].sbase <= v) lo = mid;
-          else hi = mid;
+        if (v < sb || v - sb >= sn) {
+          int32_t lo = 0, hi = a.num_inst;  // insts[lo].sbase <= v < insts[hi].sbase
+          while (hi - lo > 1) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (a.insts[mid].sbase <= v) lo = mid;
+            else hi = mid;
+          }
+          const InstDev id = a.insts[lo];
+          sb = id.sbase;
+          sn = id.n;
+          root = id.source;
+          off = a.graphs[id.graph].u_out_off;
+          dst = a.graphs[id.graph].u_out_dst;
         }
-        const InstDev id = a.insts[lo];
-        const GraphDev &G = a.graphs[id.graph];
-        sb = id.sbase;
-        root = id.source;
-        dst = G.u_out_dst;
-        k0 = G.u_out_off[v - sb];
-        k1 = G.u_out_off[v - sb + 1];
+        k0 = off[v - sb];
+        k1 = off[v - sb + 1];
         if (k1 - k0 <= kBackScan) {
           // four out-edges at a time, each step's loads issued together
           // (past the list's end a lane reads edge kb again and its test
@@ -444,7 +453,7 @@ hipError_t launch_backward(const BackArgs &a, int32_t max_inst, int32_t max_n,
   hipLaunchKernelGGL(bw_parent_kernel, pg, dim3(BBS), 0, stream, a);
   // Each instance on one XCD keeps what its walkers read in that XCD's L2, but
   // takes its vertices from a counter and needs instances enough to go round:
-  // 64 trees of 512 x 512 (16.8 M vertices) 3.2 -> 2.0 ms, 256 of 30011 2.05 ->
+  // 64 trees of 512 x 512 (16.8 M vertices) 3.2 -> 1.8 ms, 256 of 30011 2.05 ->
   // 1.57 (the whole pass), 8 of 10^6 1.60 -> 1.65, 64 of 30011 0.49 -> 0.54, 16
   // of 30011 0.13 -> 0.18.
   if (a.total >= (1 << 22) && (int64_t)max_n * 16 <= a.total) {
