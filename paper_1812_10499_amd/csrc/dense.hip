@@ -42,7 +42,6 @@ typedef int32_t edge_pair __attribute__((ext_vector_type(4), aligned(8)));
 
 struct DenseArgs {
   int32_t K, teams;
-  int32_t wide;               // one team of K blocks over all XCDs
   unsigned long long *words;  // [teams][2 K + 1]: offers, round ends, the next instance
   int32_t *queue;             // instances taken beyond the first of each team
 };
@@ -80,13 +79,17 @@ __device__ __forceinline__ T *scalar_ptr(T *p) {
   return (T *)(uintptr_t)readlane64((int64_t)(uintptr_t)p, 0);
 }
 
-template <class V, bool BATCH>
+// WIDE: one instance, by one team of q.K blocks (up to kMaxWide) over all XCDs.
+// Every wait reads as many words as the widest team of its form has blocks: one
+// a lane here, four where WIDE.  That is the team's width and nothing else: a
+// batch of one instance may be as wide as a single solve.
+template <class V, bool BATCH, bool WIDE>
 __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArgs q) {
   __shared__ DenseLds s;
   const int tid = threadIdx.x, wv = tid / SSSP_WAVE, l = lane_id();
   const int tb = blockIdx.x >> 3, K = q.K;
-  const int j = q.wide ? (int)blockIdx.x : tb % K;
-  const int team = q.wide ? 0 : (tb / K) * 8 + (int)(blockIdx.x & 7u);
+  const int j = WIDE ? (int)blockIdx.x : tb % K;
+  const int team = WIDE ? 0 : (tb / K) * 8 + (int)(blockIdx.x & 7u);
   if (team >= q.teams) return;
   unsigned long long *pub = q.words + (size_t)team * (2 * K + 1);
   unsigned long long *fin = pub + K, *nxt = fin + K;
@@ -110,7 +113,8 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
       if (l == 0) put64(&words[j], offers(ep, md, th), same);
       bool lo = false;
       md = th = 0x7fffffff;
-      if (BATCH || K <= SSSP_WAVE) {  // (a batch's teams are of one XCD)
+      if constexpr (!WIDE) {
+        static_assert(kMaxTeamBlocks <= SSSP_WAVE, "a word a lane");
         const unsigned long long x = await_offers(words, l < K ? l : 0, ep, &lo);
         md = offers_md(x);
         th = offers_th(x);
@@ -124,7 +128,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int b = i * SSSP_WAVE + l;
-            x[i] = ld_relaxed64(&words[b < K ? b : l]);
+            x[i] = ld_relaxed64(&words[b < K ? b : 0]);
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i) wait |= (unsigned)(x[i] >> 62) != (ep & 3u);
@@ -312,7 +316,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
         // the words are rewritten by the team's next instance: only after
         // every block has read them
         int32_t z0 = 0, z1 = 0;
-        if (BATCH) team_min(fin, z0, z1, false);
+        if (BATCH && !WIDE) team_min(fin, z0, z1, false);
         break;
       }
       ++bounds;
@@ -506,7 +510,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
     }
     // ---- the next instance: the team's first block takes it from the queue
     ++ep;
-    if (!BATCH) break;
+    if (!BATCH || WIDE) break;
     if (wv == 0) {
       int32_t next = 0;
       if (j == 0) {
@@ -549,7 +553,7 @@ __global__ void dense_counts_kernel(RoundArgs a) {
     for (int k = 0; k < 4; ++k) a.istat[4 * i + k] = 0;
 }
 
-// From here a single solve runs as one team over all XCDs (agent-scope stores,
+// From here one instance runs as one team over all XCDs (agent-scope stores,
 // 256 words a barrier), below as one on an XCD: 30000 vertices of degree 8 take
 // 0.30 ms on one, 0.33 on all; 40000 0.38 and 0.37; 150001 0.93 and 0.51.
 constexpr int32_t kWideFrom = 36864;
@@ -562,23 +566,32 @@ constexpr int32_t kWideFrom = 36864;
 constexpr int32_t kDensePerBlock = 1024, kDenseMostPerBlock = 8192;
 constexpr int kDenseQueueBlocks = 16;
 
+// Co-resident blocks per compute unit (0: none).
+template <class V, bool BATCH, bool WIDE>
+static hipError_t dense_occupancy(int *occ) {
+  static std::atomic<int> known{0};
+  hipError_t e = hipSuccess;
+  if ((*occ = known.load()) == 0) {
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        occ, (const void *)dense_rounds_kernel<V, BATCH, WIDE>, DBS, 0);
+    if (e == hipSuccess) known.store(*occ);
+  }
+  return e;
+}
+
 template <class V, bool BATCH>
 static hipError_t launch_dense_t(const RoundArgs &a, const LaunchGeom &geo, int32_t max_n,
                                  const KernelTimer *timer, Launcher &L, bool *done) {
   *done = false;
   hipError_t e;
-  static std::atomic<int> known{0};  // co-resident blocks per compute unit
-  int occ = known.load();
-  if (occ == 0) {
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-             &occ, (const void *)dense_rounds_kernel<V, BATCH>, DBS, 0)) != hipSuccess)
-      return e;
-    if (occ < 1) return hipSuccess;
-    known.store(occ);
-  }
+  const bool wide = a.num_inst == 1 && max_n > kWideFrom;
+  int occ = 0;
+  if ((e = wide ? dense_occupancy<V, BATCH, true>(&occ)
+                : dense_occupancy<V, BATCH, false>(&occ)) != hipSuccess)
+    return e;
+  if (occ < 1) return hipSuccess;
   const int blocks = geo.blocks < geo.cus ? geo.blocks : geo.cus;  // one per compute unit
   int K = blocks / 8 < kMaxTeamBlocks ? blocks / 8 : kMaxTeamBlocks;
-  const int wide = a.num_inst == 1 && max_n > kWideFrom ? 1 : 0;
   if (wide) K = blocks < kMaxWide ? blocks : kMaxWide;
   if (K < 1 || (int64_t)max_n > (int64_t)K * DBS * kDenseSlots) return hipSuccess;
   if (!wide) {
@@ -596,7 +609,6 @@ static hipError_t launch_dense_t(const RoundArgs &a, const LaunchGeom &geo, int3
   DenseArgs q;
   q.K = K;
   q.teams = teams;
-  q.wide = wide;
   q.words = (unsigned long long *)a.flags;
   q.queue = a.part;
   RoundArgs arg = a;
@@ -614,9 +626,9 @@ static hipError_t launch_dense_t(const RoundArgs &a, const LaunchGeom &geo, int3
   if (L.graph) timer = nullptr;
   if (timer && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
   const unsigned grid = wide ? (unsigned)K : (unsigned)((teams + 7) / 8) * 8u * (unsigned)K;
-  if ((e = launch_kernel(L, (const void *)dense_rounds_kernel<V, BATCH>, dim3(grid), dim3(DBS),
-                         params, true)) != hipSuccess)
-    return e;
+  const void *fn = wide ? (const void *)dense_rounds_kernel<V, BATCH, true>
+                        : (const void *)dense_rounds_kernel<V, BATCH, false>;
+  if ((e = launch_kernel(L, fn, dim3(grid), dim3(DBS), params, true)) != hipSuccess) return e;
   if (timer && (e = hipEventRecord(timer->stop, L.stream)) != hipSuccess) return e;
   *done = true;
   return hipSuccess;

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import gen
+import oracle
 from gpu_util import assert_same_solution, oracle_solution, sync, to_np
 
 pytestmark = pytest.mark.gpu
@@ -144,6 +145,53 @@ def test_batches(sp, count, lo, hi, kind):
         sl = slice(bases[i], bases[i] + g.n)
         assert_same_solution(torch.from_numpy(out[0][0][sl]), torch.from_numpy(out[0][1][sl]),
                              out[0][2][i], ref, "inst %d" % i)
+
+
+@pytest.mark.parametrize("n,kind,relax", [
+    (36864, 100, "setting"), (36865, 100, "setting"), (40001, "f32", "correcting"),
+    (40001, 100, "correcting"), (150001, 50, "setting"), (150001, "f32", "setting")])
+def test_batch_of_one(sp, n, kind, relax):
+    # one instance may be a team over all XCDs, whose every block has to be
+    # waited for and heard, in a batch and a plan as in a single solve; also
+    # with fewer blocks than a wave has lanes, and not a multiple of them
+    g = rand(np.random.default_rng(n), n, 8 * n, kind)
+    G = sp.Graph(g.n, g.src, g.dst, g.w, scope="all", relax=relax)
+    ref = oracle_solution(g.n, g.src, g.dst, g.w, g.source, "all", G.effective_relax,
+                          G.effective_delta)
+    for launch in (None, dict(blocks=16), dict(blocks=100)):
+        print("dense one", n, kind, relax, launch, flush=True)
+        sp.set_launch(launch)
+        try:
+            out = sp.solve(G, g.source, with_stats=True)
+            cost, pred, st = sp.solve_batch([G], [0], [g.source], with_stats=True)
+            sync()
+        finally:
+            sp.set_launch(None)
+        assert_same_solution(*out, ref, "single %s" % launch)
+        assert_same_solution(cost, pred, st[0], ref, "batch %s" % launch)
+    plan = sp.Plan([G], [0], [g.source], with_stats=True)
+    for _ in range(3):  # replays, with eager work and a synchronization between
+        plan.cost.zero_()
+        plan.run()
+        sync()
+        assert_same_solution(plan.cost, plan.pred, plan.stats()[0], ref, "plan")
+    plan.close()
+    sp.check()
+
+
+def test_training_step_of_one_source(sp):
+    n = 40001
+    g = rand(np.random.default_rng(3), n, 8 * n, "f32")
+    G = sp.Graph(g.n, g.src, g.dst, g.w)
+    assert G.effective_scope == "all"
+    w = torch.from_numpy(g.w).cuda().requires_grad_()
+    ref = oracle_solution(g.n, g.src, g.dst, g.w, g.source)
+    cost = sp.shortest_paths(w, G, [g.source], order="coo")
+    (gw,) = torch.autograd.grad(cost.sum(), w)
+    assert np.array_equal(to_np(cost)[0], ref["cost"])
+    # unit coefficients: whole numbers, exact in any order
+    want = oracle.grad(ref["csr"], [g.source], ref["pred"].reshape(1, n), np.ones((1, n)))
+    assert np.array_equal(to_np(gw)[to_np(G.perm)].astype(np.float64), want)
 
 
 def test_watchdog(sp):
