@@ -23,7 +23,11 @@ namespace sssp {
 
 constexpr int kRegEdges = 4;   // a vertex's lightest in-edges kept in registers
 constexpr int kItemLanes = 8;  // lanes that share a relax item's out-list
-constexpr int32_t kLongOut = 64;  // longer out-lists are relaxed by the whole block
+// Longer out-lists are relaxed by a wave each, these by the whole block.  All
+// of them one after another by the whole block, 4096 vertices of degree 64,
+// 256 and 1000 take 1766, 4852 and 4493 us, this way 542, 805 and 2478.  The
+// line at 32 or 16: 212 and 230 us at degree 32 (180 at 64), 500 at degree 64.
+constexpr int32_t kLongOut = 64, kHugeOut = 1024;
 
 // The open set O is implicit: y is open iff it is discovered (D < INF) and
 // not fixed (C < INF; fixed vertices carry C = INF, and a discovered vertex
@@ -35,9 +39,9 @@ struct SmallLds {
   int32_t DR[N];            // D of the last relax, or of the coming one (INF: never)
   int32_t off[N + 1];       // out-offsets
   uint16_t F[N];            // relax set
-  uint16_t L[N];            // its members with long out-lists
+  uint16_t L[N];            // its members with long out-lists, the huge ones from the end
   int32_t red[2][2 * NW];   // by round parity
-  int32_t nF, nL, target_hit, ndegen;
+  int32_t nF, nL, nH, target_hit, ndegen;
   unsigned long long relaxed, scanned, visits, settled;
 };
 
@@ -159,7 +163,7 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
     s.off[n] = G.out_off[n];
     s.F[0] = (uint16_t)src;
     s.nF = 1;
-    s.nL = 0;
+    s.nL = s.nH = 0;
     s.ndegen = 0;
     s.target_hit = (tgt >= 0 && tgt == src) ? 1 : 0;
     s.relaxed = s.scanned = s.visits = 0ull;
@@ -182,8 +186,8 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
     // it joined the set (first discoveries join O by getting a finite D):
     // kItemLanes lanes to an item, two items at a time
     const int nF = s.nF;
-    auto relax_edge = [&](int32_t dx, int32_t pos) {
-      const int4 er = G.out_rec[pos];  // head, weight, edge id, the head's out_wmin
+    auto relax_edge = [&](int32_t dx, const int4 &er) {
+      // er: head, weight, edge id, the head's out_wmin
       const int32_t cand = V::add(dx, er.y);
       atomicMin(&s.D[er.x], make_key(cand, er.z, cand == dx));
     };
@@ -203,7 +207,8 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
             dx[u] = s.DR[x];
             if (l == 0) {
               nrel += (unsigned long long)(e[u] - b[u]);
-              if (e[u] - b[u] > kLongOut) s.L[atomicAdd(&s.nL, 1)] = (uint16_t)x;
+              if (e[u] - b[u] > kHugeOut) s.L[N - 1 - atomicAdd(&s.nH, 1)] = (uint16_t)x;
+              else if (e[u] - b[u] > kLongOut) s.L[atomicAdd(&s.nL, 1)] = (uint16_t)x;
             }
             if (e[u] - b[u] > kLongOut) e[u] = b[u];
           }
@@ -215,21 +220,34 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
             if (b[u] + k < e[u]) er[u] = G.out_rec[b[u] + k];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            if (b[u] + k < e[u]) {
-              const int32_t cand = V::add(dx[u], er[u].y);
-              atomicMin(&s.D[er[u].x], make_key(cand, er[u].z, cand == dx[u]));
-            }
+            if (b[u] + k < e[u]) relax_edge(dx[u], er[u]);
           }
         }
       }
     }
     __syncthreads();
-    const int nL = s.nL;
-    if (nL > 0) {
-      for (int i = 0; i < nL; ++i) {
+    const int nL = s.nL, nH = s.nH;
+    if (nL + nH > 0) {
+      constexpr int U = 4;
+      for (int i = tid / SSSP_WAVE; i < nL; i += NW) {
         const int x = s.L[i];
-        const int32_t e = s.off[x + 1], dx = s.DR[x];
-        for (int32_t k = s.off[x] + tid; k < e; k += T) relax_edge(dx, k);
+        const int4 *rec = G.out_rec + s.off[x];
+        const int32_t deg = s.off[x + 1] - s.off[x], dx = s.DR[x];
+        for (int32_t k = lane_id(); k < deg; k += U * SSSP_WAVE) {
+          int4 er[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (k + u * SSSP_WAVE < deg) er[u] = rec[k + u * SSSP_WAVE];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (k + u * SSSP_WAVE < deg) relax_edge(dx, er[u]);
+        }
+      }
+      for (int i = 0; i < nH; ++i) {
+        const int x = s.L[N - 1 - i];
+        const int4 *rec = G.out_rec + s.off[x];
+        const int32_t deg = s.off[x + 1] - s.off[x], dx = s.DR[x];
+        for (int32_t k = tid; k < deg; k += T) relax_edge(dx, rec[k]);
       }
       __syncthreads();
     }
@@ -270,7 +288,7 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
       }
     }
     if (md == V::INF) break;  // (A) left nothing open
-    if (tid == 0) s.nL = 0;
+    if (tid == 0) s.nL = s.nH = 0;
     // (C) lower bounds (Eq. 1), Jacobi over C[cur]; SP_4's scope also
     // raises C of undiscovered vertices (an unreachable one, C = INF, keeps
     // it).  In-lists ascend by weight and every term max(C[v], minD) + w is

@@ -107,3 +107,27 @@ def test_small_batch_watchdog(sp):
     cost, _, _ = sp.solve_batch([G], [0, 0], [0, 0])
     sp.check()
     assert torch.equal(cost[:g.n], cost[g.n:])
+
+
+@pytest.mark.parametrize("n", [1000, 2011, 4090])
+def test_long_out_lists(sp, n):
+    # out-degrees around the lines between 8 lanes, a wave and the whole block
+    # to an out-list, several of each in one relax set
+    rng = np.random.default_rng(n)
+    degs = [1, 7, 8, 9, 63, 64, 65, 127, 256, 257, 1023, 1024, 1025, 1100, 2500]
+    tails = rng.permutation(n)[:3 * len(degs)]
+    src = [np.zeros(len(tails), np.int64), np.repeat(tails, np.tile(degs, 3))]
+    dst = [tails, rng.integers(0, n, 3 * sum(degs))]
+    src += [rng.integers(0, n, 2 * n)]
+    dst += [rng.integers(0, n, 2 * n)]
+    src, dst = np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)
+    w = rng.integers(1, 4, len(src)).astype(np.int32)
+    for scope, relax in (("open", "setting"), ("all", "correcting")):
+        G = sp.Graph(n, src, dst, w, scope=scope, relax=relax)
+        ref = oracle_solution(n, src, dst, w, 0, scope, G.effective_relax, G.effective_delta)
+        print("long lists", n, scope, relax, flush=True)
+        cost, pred, st = sp.solve(G, 0, with_stats=True)
+        bc, bp, bst = sp.solve_batch([G], [0, 0], [0, int(tails[-1])], with_stats=True)
+        sync()
+        assert_same_solution(cost, pred, st, ref, "single")
+        assert_same_solution(bc[:n], bp[:n], bst[0], ref, "batch")
