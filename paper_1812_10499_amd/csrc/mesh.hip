@@ -494,13 +494,18 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
   }
 }
 
-// Waves per team: one per kMeshPerWave vertices (a 66 x 66 grid takes 0.64 ms
-// on 8 waves, 0.74 on 4, 0.77 in one workgroup), at most 64 (a lane reads one
-// wave's words; a 1024 x 1024 grid takes 22.4 ms on 64, 27.8 on 32).  All
-// teams together kMeshWavesPerCu waves per compute unit: 64 solves of a 384 x
+// Waves per team: one per kMeshPerWave vertices, and more while all teams
+// together have at most kMeshRoomy (two a compute unit): they hold wider open
+// sets, and cost nothing.  Single solves on 8, 16, 32 waves and in one
+// workgroup: 70 x 70 grid 733, 694, 675, 883 us; 20^3 mesh 936 (gives up), 564,
+// 482, 723; random 3-regular on 5000 vertices 333 (gives up), 352 (gives up),
+// 165, 244.  16 solves of a 66 x 66 grid 938, 897, 913, 1119, 64 of them 979,
+// 994, 1045, 1132.  At most 64 (a lane reads one wave's words; a 1024 x 1024 grid
+// takes 22.4 ms on 64, 27.8 on 32).  All teams together kMeshWavesPerCu waves per compute unit: 64 solves of a 384 x
 // 384 grid take 4.8 ms at 8, 5.3 at 4 and 11.5 at 2 (seats fill up), 5.8 in
 // one workgroup each.
 constexpr int32_t kMeshPerWave = 512;
+constexpr int kMeshRoomy = 512;
 constexpr int kMeshWavesPerCu = 8;
 
 // Teams for this solve, or false: the one-workgroup kernel takes it.
@@ -524,8 +529,11 @@ static bool mesh_plan(const RoundArgs &a, const LaunchGeom &geo, int32_t max_n, 
   // the redo words lie in the per-block partials, the team words in the
   // barrier flags, the mailboxes in the open lists' payload
   if (a.num_inst > kParts * kMaxBlocks) return false;
+  if (max_n < 2 * kMeshPerWave) return false;
   int lw = 0;
-  while (lw < 6 && ((int64_t)2 << lw) * kMeshPerWave <= (int64_t)max_n) ++lw;
+  while (lw < 6 && (((int64_t)2 << lw) * kMeshPerWave <= (int64_t)max_n ||
+                    ((int64_t)2 << lw) * a.num_inst <= kMeshRoomy))
+    ++lw;
   for (; lw >= 1; --lw) {
     const int64_t W = (int64_t)1 << lw;
     int64_t teams = blocks / (8 * W) * 8;  // whole sets of eight teams
