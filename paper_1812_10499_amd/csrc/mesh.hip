@@ -34,8 +34,12 @@
 //     own.
 // A mailbox or a wave's seats can fill up (large open sets).  The wave says so
 // with its next word, the whole team leaves, and the one-workgroup kernel,
-// launched behind this one, runs that instance from its start; it skips the
-// others.
+// launched behind this one, goes on with that instance at the bound step of
+// the round that did not fit; it skips the others.  It finds nearly all it needs
+// in memory.  What else a team left there as it goes (the counts before each
+// bound step, the D of each relax) cost a 1024 x 1024 grid 2 to 4 % of its time,
+// and so did the same exits without the hints on their likelihood: a wave is
+// alone on its SIMD, and every jump on its way counts.
 #include <atomic>
 
 #include "sssp_dev.h"
@@ -66,7 +70,10 @@ __device__ __forceinline__ int mesh_owner(int32_t y, int lw) {
 struct MeshArgs {
   int32_t lw, teams;
   unsigned long long *words, *box0, *box1;
-  int32_t *redo;  // per instance: the one-workgroup kernel is to run it
+  // per instance: the round the one-workgroup kernel goes on with (a mailbox was
+  // full; negative: the seats were, and the round's bound step has run for the
+  // vertices that had one), or 0
+  int32_t *redo;
 };
 
 // D = INF, C = 0, the sources, empty words and mailboxes, the control block
@@ -89,6 +96,7 @@ __global__ __launch_bounds__(256) void mesh_init_kernel(RoundArgs a, MeshArgs q)
     const bool is_s = y == src;
     a.D64[sb + y] = make_key(is_s ? 0 : V::INF, -1, false);
     a.C0[sb + y] = a.C1[sb + y] = is_s ? V::INF : 0;  // the source is fixed from the start
+    if (G.lc) a.DR[sb + y] = V::INF;
   }
   if (t0 == 0) {
     q.redo[inst] = 0;
@@ -212,16 +220,16 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
     unsigned long long nrel = 0, nscan = 0;
     uint32_t nvis = 0, nfix = 0;
     int32_t smd = V::INF, sth = V::INF;
-    bool full = false, gave_up = false, hit = tgt >= 0 && tgt == src;
-    int r = 0, status = 0;
+    bool full = false, hit = tgt >= 0 && tgt == src;
+    int r = 0, status = 0, gave_up = 0;
     // the first edge of this lane's first relax item, read ahead
     int4 er = make_int4(0, 0, 0, 0);
     bool ahead = false;
     for (;;) {
-      if (hit) break;  // the frontier that fixed the target is not relaxed
+      if (__builtin_expect(hit, 0)) break;  // the frontier that fixed the target is not relaxed
       ++r;
       ++ep;
-      if (r > n + 1 || r > a.max_rounds) {  // (every wave alike)
+      if (__builtin_expect(r > n + 1 || r > a.max_rounds, 0)) {  // (every wave alike)
         status = 7;
         break;
       }
@@ -243,7 +251,7 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
           if (e0 == 0) nrel += (unsigned long long)deg;
           for (int32_t k = e0; k < deg; k += kMeshLanes) {
             // head, weight, edge id, the head's out_wmin
-            if (i0 > 0 || k != e0 || !ahead) er = G.out_rec[f.z + k];
+            if (__builtin_expect(i0 > 0 || k != e0 || !ahead, 0)) er = G.out_rec[f.z + k];
             const int32_t cand = V::add(dx, er.y);
             const unsigned long long old =
                 atomicMin(&D[er.x], make_key(cand, er.z, cand == dx));
@@ -255,7 +263,7 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
             if (od == V::INF) {  // a first discovery
               const int o = mesh_owner(er.x, lw);
               const int p = atomicAdd(&s.sent[o], 1);
-              if (p < kBox) put64(&box[((size_t)o * kBox + p) * W + w], tagged(ep, er.x), same);
+              if (__builtin_expect(p < kBox, 1)) put64(&box[((size_t)o * kBox + p) * W + w], tagged(ep, er.x), same);
               else full = true;
             }
           }
@@ -270,9 +278,9 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
         md = wave_min(offers_md(x));
         th = wave_min(offers_th(x));
       }
-      if (lost) break;
-      if (md == kGiveUp || md == V::INF) {  // (every wave alike)
-        gave_up = md == kGiveUp;
+      if (__builtin_expect(lost, 0)) break;
+      if (__builtin_expect(md == kGiveUp || md == V::INF, 0)) {  // (every wave alike)
+        gave_up = md == kGiveUp ? r : 0;
         // the words are rewritten by the team's next instance: only after
         // every wave has read them
         if (l == 0) put64(&read_d[w], tagged(ep, 0), same);
@@ -309,7 +317,7 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
         nmsg = __popcll(b0);
         if (v1) s.msg[nmsg + __popcll(b1 & lt)] = (int32_t)(uint32_t)m1;
         nmsg += __popcll(b1);
-        for (int k = 2; k < kBox && __ballot(v1); ++k) {
+        for (int k = 2; k < kBox && __builtin_expect(__ballot(v1) != 0ull, 0); ++k) {
           const unsigned long long m = ld_relaxed64(&box[((size_t)w * kBox + k) * W + lp]);
           v1 = v1 && (unsigned)(m >> 32) == ep;
           const uint64_t b = __ballot(v1);
@@ -395,7 +403,8 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
           for (int e = 0; e < kMeshEdges; ++e)
             if (cv[u][e] != V::INF && V::add(md, ew[u][e]) < dy)
               m = kmin(m, V::add(kmax(cv[u][e], md), ew[u][e]));
-          if (ideg[u] > kMeshEdges && V::add(md, ew[u][kMeshEdges - 1]) < kmin(dy, m)) {
+          if (__builtin_expect(ideg[u] > kMeshEdges, 0) &&
+              V::add(md, ew[u][kMeshEdges - 1]) < kmin(dy, m)) {
             for (int32_t j = kMeshEdges; j < ideg[u]; ++j) {
               const int2 e = G.in_sw[ioff[u] + j];  // tail, weight
               if (V::add(md, e.y) >= kmin(dy, m)) break;
@@ -450,9 +459,9 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
           put64(&read_d[w], tagged(ep, (h ? kReadHit : 0) | (full ? kReadFull : 0)), same);
       }
       const int32_t flags = await_read();
-      if (lost) break;
-      if (flags & kReadFull) {
-        gave_up = true;
+      if (__builtin_expect(lost, 0)) break;
+      if (__builtin_expect((flags & kReadFull) != 0, 0)) {
+        gave_up = -r;
         break;
       }
       hit = (flags & kReadHit) != 0;
@@ -461,9 +470,26 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
       if (l == 0) atomicMax(&a.ctl->status, 7);
       return;
     }
-    if (gave_up) {
-      if (w == 0 && l == 0) q.redo[inst] = 1;
-      continue;
+    if (w == 0 && l == 0) q.redo[inst] = gave_up;
+    if (__builtin_expect(gave_up != 0 && lc, 0)) {
+      // DR: the D that each open vertex was last relaxed with.  The seats have
+      // it, and for a vertex that this round's bound step put into the relax set,
+      // which is to decide again, INF or 0 (above its D, or not) does.
+      // (its address is read from the kernel's arguments here: kept over the
+      // rounds in scalar registers it would push the loop's own out of them)
+      const RoundArgs *args = (const RoundArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(args));
+      int32_t *DR = args->DR + sb;
+#pragma unroll
+      for (int u = 0; u < kSeats; ++u)
+        if (y[u] >= 0) put(&DR[y[u]], dr[u], same);
+      stores_done();
+      if (gave_up < 0) {
+        for (int i = l; i < nF; i += SSSP_WAVE) {
+          const int4 f = s.rel[i];
+          put(&DR[f.x], f.y != V::INF ? V::INF : 0, same);
+        }
+      }
     }
     const long long v0 = wave_sum64((long long)nrel), v1 = wave_sum64((long long)nscan);
     const long long v2 = wave_sum64((long long)nvis), v3 = wave_sum64((long long)nfix);
@@ -578,11 +604,11 @@ static hipError_t launch_mesh_t(const RoundArgs &a, const LaunchGeom &geo, int32
                               : (const void *)mesh_rounds_kernel<V, BATCH, 4>;
   if ((e = launch_kernel(L, fn, dim3(grid), dim3(SSSP_WAVE), params, true)) != hipSuccess)
     return e;
-  if (timer && (e = hipEventRecord(timer->stop, L.stream)) != hipSuccess) return e;
   *redo = q.redo;
   return hipSuccess;
 }
 
+// (the timer is stopped behind launch_wg, which may have a part of the rounds)
 hipError_t launch_mesh(bool f32, bool batch, const RoundArgs &a, const LaunchGeom &geo,
                        int32_t max_n, const KernelTimer *timer, Launcher &L,
                        const int32_t **redo) {

@@ -230,8 +230,8 @@ hipError_t round_kernel_occupancy(bool f32, bool batch, int *blocks_per_cu);
 constexpr size_t kScratchBytes = (size_t)64 << 20;
 hipError_t scratch_address(void **ptr);
 // every instance's rounds in a workgroup of its own (C scope OPEN), then the
-// emit pass; redo (nullable): per instance, whether to run it at all (the
-// team kernel before it has run the others)
+// emit pass; redo (nullable): per instance, the round to go on with where the
+// team kernel before it stopped, 0 where that finished
 hipError_t launch_wg(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
                      const LaunchGeom &geo, long long *istat, int32_t max_n,
                      const KernelTimer *timer, Launcher &L, const int32_t *redo);
@@ -241,8 +241,8 @@ hipError_t launch_wg(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
 hipError_t launch_dense(bool f32, bool batch, const RoundArgs &a, const LaunchGeom &geo,
                         int32_t max_n, const KernelTimer *timer, Launcher &L, bool *done);
 // every instance's rounds by a team of single-wave workgroups (C scope OPEN);
-// *redo: the instances launch_wg has to run, or null: nothing was launched
-// (teams do not fit)
+// *redo: what launch_wg has to go on with, or null: nothing was launched (teams
+// do not fit).  launch_wg stops the timer
 hipError_t launch_mesh(bool f32, bool batch, const RoundArgs &a, const LaunchGeom &geo,
                        int32_t max_n, const KernelTimer *timer, Launcher &L,
                        const int32_t **redo);

@@ -6,7 +6,8 @@
 // For graphs of low degree spread under C scope OPEN (meshes, grids), whose
 // rounds are many and small; the rounds, counters and keys are those of the
 // persistent kernel (Section VI's rounds in the adopted order: relax, minD
-// and the threshold, the lower bounds of Eq. 1, fix).
+// and the threshold, the lower bounds of Eq. 1, fix).  Behind the team kernel
+// of mesh.hip it goes on with the instances that outgrew their team.
 #include "sssp_dev.h"
 #include "sssp_kernels.h"
 
@@ -53,6 +54,9 @@ __device__ __forceinline__ void push_rel(WgLds &s, int32_t *F, int32_t *FD, int3
   }
 }
 
+// redo (nullable): per instance the round to go on with, from behind its relax
+// (0: the instance is done; negative: the team has run that round's bound step
+// for part of the vertices), with D, C, DR and the counts as the team left them.
 template <class V, bool BATCH>
 __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32_t *redo) {
   __shared__ WgLds s;
@@ -70,7 +74,8 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     c->status = 0;
   }
   for (int inst = blockIdx.x; inst < a.num_inst; inst += gridDim.x) {
-    if (redo && !redo[inst]) continue;
+    const int left = redo ? redo[inst] : 0, r0 = left < 0 ? -left : left;
+    if (redo && !r0) continue;
     int32_t sb = 0, gi = 0, src = a.source, n = a.g.n;
     if constexpr (BATCH) {
       const InstDev id = a.insts[inst];
@@ -103,7 +108,7 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     // than gathered
     int32_t *O[2] = {a.open_v0 + sb, a.open_v1 + sb};
     int32_t *OR[2] = {a.open_p0 + sb, a.open_p1 + sb};
-    for (int y = tid; y < n; y += WBS) {
+    for (int y = r0 ? n : tid; y < n; y += WBS) {
       const bool is_s = y == src;
       D[y] = make_key(is_s ? 0 : V::INF, -1, false);
       C[0][y] = C[1][y] = is_s ? V::INF : 0;  // the source is fixed from the start
@@ -111,11 +116,18 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     if (tid == 0) {
       const int32_t o0 = G.out_off[src];
       s.rel[0] = make_int4(src, 0, o0, G.out_off[src + 1] - o0);
-      s.nF = 1;
+      s.nF = r0 ? 0 : 1;
       s.nO = 0;
       s.target_hit = (tgt >= 0 && tgt == src) ? 1 : 0;
       s.relaxed = s.scanned = s.visits = 0ull;
       s.settled = 1ull;  // the source
+      if (r0) {  // the team's counts (a batch takes settled from the emit pass)
+        const Ctl *c = a.ctl;
+        s.relaxed = BATCH ? a.iscanned[3 * inst + 2] : (unsigned long long)c->relaxed;
+        s.scanned = BATCH ? a.iscanned[3 * inst] : (unsigned long long)c->scanned;
+        s.visits = BATCH ? a.iscanned[3 * inst + 1] : (unsigned long long)c->open_visits;
+        s.settled = (unsigned long long)c->settled;
+      }
     }
     __syncthreads();
     // minD / thr offers of this thread's survivors of the last fix step:
@@ -123,7 +135,59 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     // current D (a survivor whose D fell offered the lower value as a
     // candidate), so no pass over the open list is needed for them
     int32_t smd = V::INF, sth = V::INF;
-    int r = 0, o = 0, status = 0;  // o: the open list being built this round
+    if (r0) {
+      // the open list as a round would find it whose relax set is empty: every
+      // open vertex a survivor with its payload and its offers.  The bound step
+      // runs again as a whole: it reads C[r0 & 1] and writes the other buffer,
+      // so a vertex that the team had come to (whose C there is no longer 0) is
+      // only taken off the counts.  What was fixed before is marked in both.
+      const int32_t *Cold = C[r0 & 1];
+      int32_t *Cnew = C[(r0 & 1) ^ 1];
+      long long scan = 0, vis = 0, fix = 0;
+      int4 *P = wg_payload(a, 0, sb), *Q = P + a.total;
+      constexpr int U = 4;
+      for (int y0 = tid; y0 < n; y0 += U * WBS) {
+        int32_t d[U], c[U], c1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = y0 < n - u * WBS;
+          d[u] = in ? (int32_t)(D[y0 + u * WBS] >> 32) : V::INF;
+          c[u] = in ? Cold[y0 + u * WBS] : V::INF;
+          c1[u] = in ? Cnew[y0 + u * WBS] : V::INF;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int y = y0 + u * WBS;
+          if (c[u] == V::INF && c1[u] != V::INF) Cnew[y] = V::INF;
+          if (d[u] == V::INF || c[u] == V::INF) continue;
+          const int4 ra = G.vrec[2 * y];
+          int4 rb = G.vrec[2 * y + 1];
+          const int q = atomicAdd(&s.nO, 1);
+          O[0][q] = y;
+          P[q] = ra;
+          rb.w = c[u];
+          if (left < 0 && c1[u] != 0) {
+            scan += ra.w;
+            ++vis;
+            fix += c1[u] == V::INF ? 1 : 0;
+          }
+          Q[q] = rb;
+          OR[0][q] = lc ? a.DR[sb + y] : V::INF;
+          smd = kmin(smd, d[u]);
+          sth = kmin(sth, V::add(d[u], rb.x));
+        }
+      }
+      scan = wave_sum64(scan);
+      vis = wave_sum64(vis);
+      fix = wave_sum64(fix);
+      if (lane_id() == 0 && vis) {
+        atomicAdd(&s.scanned, 0ull - (unsigned long long)scan);
+        atomicAdd(&s.visits, 0ull - (unsigned long long)vis);
+        atomicAdd(&s.settled, 0ull - (unsigned long long)fix);
+      }
+      __syncthreads();
+    }
+    int r = r0 ? r0 - 1 : 0, o = 0, status = 0;  // o: the open list being built this round
     for (;;) {
       if (tgt >= 0 && s.target_hit) break;  // the frontier that fixed it is not relaxed
       ++r;
@@ -388,11 +452,11 @@ static hipError_t launch_wg_t(const RoundArgs &a, int32_t *pred, const LaunchGeo
   if (a.scope_all) return hipErrorInvalidValue;  // the live pass is not here
   RoundArgs arg = a;
   void *params[] = {&arg, &redo};
-  if (redo) timer = nullptr;  // (the team kernel was the timed one)
   int blocks = a.num_inst < geo.blocks ? a.num_inst : geo.blocks;
   if (blocks < 1) blocks = 1;
   if (L.graph) timer = nullptr;
-  if (timer && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
+  // (behind a team kernel the timer runs already)
+  if (timer && !redo && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
   if ((e = launch_kernel(L, (const void *)wg_rounds_kernel<V, BATCH>, dim3(blocks), dim3(WBS),
                          params, false)) != hipSuccess)
     return e;

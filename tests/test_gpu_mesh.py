@@ -82,6 +82,65 @@ def test_room_runs_out(sp, k, f32):
     three_ways(sp, regular(np.random.default_rng(k), 20000, k, f32), "regular%d" % k)
 
 
+# Open sets that no team holds, by counting alone: more open vertices a round, in
+# the mean, than 64 waves of 256 seats; or more first discoveries by one wave in
+# round 1 than 64 mailboxes of 16 hold.
+@pytest.mark.parametrize("kind,f32,kw", [
+    ("seats", False, dict()), ("seats", True, dict(order="degree")),
+    ("seats", False, dict(relax="correcting")), ("seats", False, dict(relax="correcting", delta=9)),
+    ("boxes", False, dict()), ("boxes", True, dict(relax="correcting"))])
+def test_goes_on_in_one_workgroup(sp, kind, f32, kw):
+    rng = np.random.default_rng(11)
+    if kind == "seats":
+        g = regular(rng, 160000, 7, f32)
+    else:
+        g = regular(rng, 5000, 1600, f32)
+    G, ref = three_ways(sp, g, "outgrown %s" % kind, **kw)
+    if kind == "seats":
+        assert ref["open_visits"] > 64 * 256 * ref["rounds"]
+    else:
+        first = np.unique(g.dst[(g.src == g.source) & (g.dst != g.source)])
+        assert len(first) > 64 * 16
+    # the rounds run by both kernels stop at a target as those of one do
+    order = np.argsort(ref["cost"], kind="stable")
+    for t in (int(order[1]), int(order[g.n // 2]), int(order[-1])):
+        out = []
+        for launch in (None, dict(wg=1)):
+            sp.set_launch(launch)
+            try:
+                c, st = sp.solve_target(G, g.source, t, with_stats=True)
+                sync()
+            finally:
+                sp.set_launch(None)
+            out.append((to_np(c), st))
+        assert np.array_equal(out[0][0], out[1][0]) and out[0][1] == out[1][1], t
+
+
+def test_profile_covers_both_kernels(sp):
+    # what the profiler reports of a solve that outgrew its team includes the
+    # rounds behind the team: no less than most of the one workgroup's time
+    g = regular(np.random.default_rng(12), 90000, 6)
+    G = sp.Graph(g.n, g.src, g.dst, g.w, scope="open")
+    ms = {}
+    for name, launch in (("team", None), ("one", dict(wg=1))):
+        sp.set_launch(launch)
+        try:
+            sp.solve(G, g.source)
+            sync()
+            sp.sssp_profile_read()
+            sp.sssp_profile_enable(True)
+            for _ in range(3):
+                sp.solve(G, g.source)
+            sync()
+            launches, ms[name] = sp.sssp_profile_read()
+        finally:
+            sp.sssp_profile_enable(False)
+            sp.set_launch(None)
+        assert launches == 3
+    print("profile", ms, flush=True)
+    assert ms["team"] > 0.5 * ms["one"]
+
+
 def test_target(sp):
     g = gen.grid_workload(side=80)
     G, ref = three_ways(sp, g, "target")
