@@ -54,14 +54,14 @@ __device__ __forceinline__ void push_rel(WgLds &s, int32_t *F, int32_t *FD, int3
   }
 }
 
-// redo (nullable): per instance the round to go on with, from behind its relax
+// REDO: redo holds per instance the round to go on with, from behind its relax
 // (0: the instance is done; negative: the team has run that round's bound step
 // for part of the vertices), with D, C, DR and the counts as the team left them.
-template <class V, bool BATCH>
+template <class V, bool BATCH, bool REDO>
 __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32_t *redo) {
   __shared__ WgLds s;
   const int tid = threadIdx.x;
-  if (!redo && blockIdx.x == 0 && tid == 0) {
+  if (!REDO && blockIdx.x == 0 && tid == 0) {
     // the control block the emit pass and the host read
     Ctl *c = a.ctl;
     c->front_ctr[0] = c->front_ctr[1] = 0ull;
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     c->status = 0;
   }
   for (int inst = blockIdx.x; inst < a.num_inst; inst += gridDim.x) {
-    const int left = redo ? redo[inst] : 0, r0 = left < 0 ? -left : left;
-    if (redo && !r0) continue;
+    const int left = REDO ? redo[inst] : 0, r0 = left < 0 ? -left : left;
+    if (REDO && !r0) continue;
     int32_t sb = 0, gi = 0, src = a.source, n = a.g.n;
     if constexpr (BATCH) {
       const InstDev id = a.insts[inst];
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     // than gathered
     int32_t *O[2] = {a.open_v0 + sb, a.open_v1 + sb};
     int32_t *OR[2] = {a.open_p0 + sb, a.open_p1 + sb};
-    for (int y = r0 ? n : tid; y < n; y += WBS) {
+    for (int y = REDO ? n : tid; y < n; y += WBS) {
       const bool is_s = y == src;
       D[y] = make_key(is_s ? 0 : V::INF, -1, false);
       C[0][y] = C[1][y] = is_s ? V::INF : 0;  // the source is fixed from the start
@@ -116,12 +116,12 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     if (tid == 0) {
       const int32_t o0 = G.out_off[src];
       s.rel[0] = make_int4(src, 0, o0, G.out_off[src + 1] - o0);
-      s.nF = r0 ? 0 : 1;
+      s.nF = REDO ? 0 : 1;
       s.nO = 0;
       s.target_hit = (tgt >= 0 && tgt == src) ? 1 : 0;
       s.relaxed = s.scanned = s.visits = 0ull;
       s.settled = 1ull;  // the source
-      if (r0) {  // the team's counts (a batch takes settled from the emit pass)
+      if (REDO) {  // the team's counts (a batch takes settled from the emit pass)
         const Ctl *c = a.ctl;
         s.relaxed = BATCH ? a.iscanned[3 * inst + 2] : (unsigned long long)c->relaxed;
         s.scanned = BATCH ? a.iscanned[3 * inst] : (unsigned long long)c->scanned;
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
     // current D (a survivor whose D fell offered the lower value as a
     // candidate), so no pass over the open list is needed for them
     int32_t smd = V::INF, sth = V::INF;
-    if (r0) {
+    if constexpr (REDO) {
       // the open list as a round would find it whose relax set is empty: every
       // open vertex a survivor with its payload and its offers.  The bound step
       // runs again as a whole: it reads C[r0 & 1] and writes the other buffer,
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(WBS) void wg_rounds_kernel(RoundArgs a, const int32
       }
       __syncthreads();
     }
-    int r = r0 ? r0 - 1 : 0, o = 0, status = 0;  // o: the open list being built this round
+    int r = REDO ? r0 - 1 : 0, o = 0, status = 0;  // o: the open list being built this round
     for (;;) {
       if (tgt >= 0 && s.target_hit) break;  // the frontier that fixed it is not relaxed
       ++r;
@@ -457,9 +457,9 @@ static hipError_t launch_wg_t(const RoundArgs &a, int32_t *pred, const LaunchGeo
   if (L.graph) timer = nullptr;
   // (behind a team kernel the timer runs already)
   if (timer && !redo && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
-  if ((e = launch_kernel(L, (const void *)wg_rounds_kernel<V, BATCH>, dim3(blocks), dim3(WBS),
-                         params, false)) != hipSuccess)
-    return e;
+  const void *fn = redo ? (const void *)wg_rounds_kernel<V, BATCH, true>
+                        : (const void *)wg_rounds_kernel<V, BATCH, false>;
+  if ((e = launch_kernel(L, fn, dim3(blocks), dim3(WBS), params, false)) != hipSuccess) return e;
   if (timer && (e = hipEventRecord(timer->stop, L.stream)) != hipSuccess) return e;
   return launch_pred(V::INF == KeyF32::INF, BATCH, a, pred, geo, istat, max_n, L);
 }
