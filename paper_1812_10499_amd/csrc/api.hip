@@ -217,6 +217,11 @@ bool scope_all_of(const sssp_csr *g) {
 // C scope ALL and no hubs: solves run in teams that own every vertex.
 bool dense_graph(const sssp_csr *g) { return scope_all_of(g) && g->deg_max <= kDenseDegree; }
 
+MeshClass mesh_class(const sssp_csr *g) {
+  if (g->m > (int64_t)kWideEdges * g->n) return MESH_NONE;
+  return g->m > (int64_t)kFlatEdges * g->n ? MESH_WIDE : MESH_FLAT;
+}
+
 // SSSP_RELAX_AUTO: label-correcting relax in buckets of 0.4 w_max on graphs
 // of low degree spread (largest total degree below 3m/n: the AUTO scope's
 // OPEN case) whose weights spread widely (w_max >= 16 w_min), label-setting
@@ -787,6 +792,7 @@ static void single_fill(const sssp_csr *g, int32_t source, int32_t target, void 
   a.scope_all = a.g.all;
   a.any_lc = a.g.lc;
   a.dense = dense_graph(g) ? 1 : 0;
+  a.mesh = mesh_class(g);
 }
 
 static sssp_status single_args(DevWS &ws, const sssp_csr *g, int32_t source, int32_t target,
@@ -906,7 +912,11 @@ static sssp_status batch_args(DevWS &ws, const sssp_csr *graphs, int32_t num_gra
   a.target = -1;
   a.D = (int32_t *)cost;
   a.dense = 1;
+  a.mesh = MESH_FLAT;
   for (int32_t i = 0; i < num_inst; ++i) {
+    const MeshClass mc = mesh_class(&graphs[inst_graph[i]]);
+    if (mc == MESH_NONE || a.mesh == MESH_NONE) a.mesh = MESH_NONE;
+    else if (mc == MESH_WIDE) a.mesh = MESH_WIDE;
     if (!dense_graph(&graphs[inst_graph[i]])) a.dense = 0;
     if (relax_correcting(&graphs[inst_graph[i]])) a.any_lc = 1;
     if (scope_all_of(&graphs[inst_graph[i]])) a.scope_all = 1;
@@ -1225,6 +1235,7 @@ static sssp_status plan_build(const sssp_csr *graphs, int32_t num_graphs,
       a.scope_all = a.g.all;
       a.any_lc = a.g.lc;
       a.dense = dense_graph(g) ? 1 : 0;
+      a.mesh = mesh_class(g);
       a.ctl = ctls + i;
       p->seq.push_back(a);
       p->seq_n.push_back(g->n);

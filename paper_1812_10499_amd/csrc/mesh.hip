@@ -526,12 +526,26 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
 // workgroup: 70 x 70 grid 733, 694, 675, 883 us; 20^3 mesh 936 (gives up), 564,
 // 482, 723; random 3-regular on 5000 vertices 333 (gives up), 352 (gives up),
 // 165, 244.  16 solves of a 66 x 66 grid 938, 897, 913, 1119, 64 of them 979,
-// 994, 1045, 1132.  At most 64 (a lane reads one wave's words; a 1024 x 1024 grid
+// 994, 1045, 1132.  Wide graphs get all there is room for: 32 solves of 5000
+// vertices 8-regular on 16 and 32 waves 437 and 303, 395 in one workgroup each.
+// At most 64 (a lane reads one wave's words; a 1024 x 1024 grid
 // takes 22.4 ms on 64, 27.8 on 32).  All teams together kMeshWavesPerCu waves per compute unit: 64 solves of a 384 x
 // 384 grid take 4.8 ms at 8, 5.3 at 4 and 11.5 at 2 (seats fill up), 5.8 in
 // one workgroup each.
 constexpr int32_t kMeshPerWave = 512;
 constexpr int kMeshRoomy = 512;
+// Wide graphs: four seats a lane, and beyond this many instances, whose teams
+// would be small, a workgroup each.  Against one workgroup each (and two seats):
+// one 50^3 mesh 11.3 -> 3.4 ms (6.9), 15^4 5.3 -> 1.4 (4.5), 5000 vertices
+// 8-regular 364 -> 221 us (378), 20000 5-regular 1.15 -> 0.32 ms (1.04), a 128 x
+// 128 grid with diagonals 2.5 -> 2.0 (1.9); sets that do not fit either way, an
+// 80^3 mesh 60.7 -> 43.6 (56.6), 100000 6-regular 8.6 -> 8.5 (8.7).  32 of them
+// 14.9 -> 4.8, 7.2 -> 2.1, 0.40 -> 0.30, 1.76 -> 1.1, 2.5 -> 2.2, 75.8 -> 65.8 and
+// 11.1 -> 10.8 ms.  64 and 128: 50^3 mesh 16.6 -> 17.9 and 21.1 -> 21.9, 32^3 3.6 ->
+// 2.2 and 4.0 -> 5.2.  Graphs of more than 16 edges a vertex (MESH_NONE): 5000
+// vertices of degree 40 1.31 -> 0.57, but 32 of them 1.46 -> 2.17, and 4 of
+// degree 256 7.3 -> 9.7.
+constexpr int kMeshWideMost = 32;
 constexpr int kMeshWavesPerCu = 8;
 
 // Teams for this solve, or false: the one-workgroup kernel takes it.
@@ -550,6 +564,7 @@ static bool mesh_plan(const RoundArgs &a, const LaunchGeom &geo, int32_t max_n, 
   // chip with less traffic (256 solves of a 256 x 256 grid: 4.4 ms there, 7.7
   // in teams; 128 of them: 3.6 and 3.3).
   if (2 * a.num_inst > geo.cus) return false;
+  if (a.mesh == MESH_NONE || (a.mesh == MESH_WIDE && a.num_inst > kMeshWideMost)) return false;
   const int per_cu = occ < kMeshWavesPerCu ? occ : kMeshWavesPerCu;
   const int64_t blocks = (int64_t)per_cu * (geo.blocks < geo.cus ? geo.blocks : geo.cus);
   // the redo words lie in the per-block partials, the team words in the
@@ -557,7 +572,7 @@ static bool mesh_plan(const RoundArgs &a, const LaunchGeom &geo, int32_t max_n, 
   if (a.num_inst > kParts * kMaxBlocks) return false;
   if (max_n < 2 * kMeshPerWave) return false;
   int lw = 0;
-  while (lw < 6 && (((int64_t)2 << lw) * kMeshPerWave <= (int64_t)max_n ||
+  while (lw < 6 && (a.mesh == MESH_WIDE || ((int64_t)2 << lw) * kMeshPerWave <= (int64_t)max_n ||
                     ((int64_t)2 << lw) * a.num_inst <= kMeshRoomy))
     ++lw;
   for (; lw >= 1; --lw) {
@@ -573,9 +588,13 @@ static bool mesh_plan(const RoundArgs &a, const LaunchGeom &geo, int32_t max_n, 
     q.box0 = (unsigned long long *)a.open_x0[0];
     q.box1 = (unsigned long long *)a.open_x1[0];
     q.redo = a.part;
-    // two seats a lane where a wavefront of about 4 sqrt(n) open vertices
-    // fills at most 3/5 of them
-    *seats = 16.0 * max_n <= (0.6 * 2 * SSSP_WAVE * W) * (0.6 * 2 * SSSP_WAVE * W) ? 2 : 4;
+    // two seats a lane where a wavefront of about 4 sqrt(n) open vertices fills at
+    // most 3/5 of them (four: a 1024 x 1024 grid takes 26.7 ms, not 25.6).  Where
+    // four would not hold the estimate, the team still gains until it is outgrown:
+    // 4096 x 4096 (16384 estimated, 64 x 256 seats) fits and takes 0.25 s, 1.56 in
+    // one workgroup, 8192 x 8192 4.73 before, 4.80 with the team's work lost.
+    const double room = 0.6 * 2 * SSSP_WAVE * W;
+    *seats = a.mesh == MESH_FLAT && 16.0 * max_n <= room * room ? 2 : 4;
     return true;
   }
   return false;

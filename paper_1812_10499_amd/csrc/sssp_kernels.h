@@ -146,9 +146,17 @@ struct RoundArgs {
   // every graph of the solve runs C scope ALL and has no vertex of more than
   // kDenseDegree edges (read by the host's choice of kernel)
   int32_t dense;
+  int32_t mesh;  // scope OPEN: what the solve's graphs are to teams (MeshClass)
 };
 
 constexpr int32_t kDenseDegree = 256;
+
+// MESH_FLAT: at most 4 edges a vertex, as a planar grid has: an open set of about
+// 4 sqrt(n) vertices.  MESH_WIDE: more, up to 16: 3-D meshes, whose open sets
+// grow with n^(2/3), near-regular digraphs.  MESH_NONE: a graph of more edges;
+// its solves are left to the one-workgroup kernel.
+enum MeshClass { MESH_NONE = 0, MESH_FLAT, MESH_WIDE };
+constexpr int32_t kFlatEdges = 4, kWideEdges = 16;
 
 // Trace record of one round: wall-clock (100 MHz) at the relax start, block
 // 0's arrival at and release from each of the two barriers, the list sizes

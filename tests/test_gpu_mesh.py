@@ -83,8 +83,8 @@ def test_room_runs_out(sp, k, f32):
 
 
 # Open sets that no team holds, by counting alone: more open vertices a round, in
-# the mean, than 64 waves of 256 seats; or more first discoveries by one wave in
-# round 1 than 64 mailboxes of 16 hold.
+# the mean, than 64 waves of 256 seats; or more first discoveries in round 2 than
+# the mailboxes of a team of two waves (blocks = 2) take, 16 from each to each.
 @pytest.mark.parametrize("kind,f32,kw", [
     ("seats", False, dict()), ("seats", True, dict(order="degree")),
     ("seats", False, dict(relax="correcting")), ("seats", False, dict(relax="correcting", delta=9)),
@@ -94,13 +94,17 @@ def test_goes_on_in_one_workgroup(sp, kind, f32, kw):
     if kind == "seats":
         g = regular(rng, 160000, 7, f32)
     else:
-        g = regular(rng, 5000, 1600, f32)
+        g = regular(rng, 5000, 16, f32)
+        g.w[:] = 1
     G, ref = three_ways(sp, g, "outgrown %s" % kind, **kw)
     if kind == "seats":
         assert ref["open_visits"] > 64 * 256 * ref["rounds"]
     else:
-        first = np.unique(g.dst[(g.src == g.source) & (g.dst != g.source)])
-        assert len(first) > 64 * 16
+        # unit weights: round 1 fixes the source's neighbours, round 2 discovers
+        # theirs
+        first = np.unique(g.dst[g.src == g.source])
+        second = np.unique(g.dst[np.isin(g.src, first)])
+        assert len(np.setdiff1d(second, np.append(first, g.source))) > 2 * 2 * 16
     # the rounds run by both kernels stop at a target as those of one do
     order = np.argsort(ref["cost"], kind="stable")
     for t in (int(order[1]), int(order[g.n // 2]), int(order[-1])):
