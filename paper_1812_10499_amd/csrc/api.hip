@@ -884,7 +884,12 @@ static bool all_low_spread(const sssp_csr *graphs, const int32_t *inst_graph, in
   return true;
 }
 
-// The host copies of a batch's graph and instance tables.
+// Bytes of a batch's instance table: the instances and their order.
+static size_t inst_bytes(int32_t num_inst) {
+  return (sizeof(InstDev) + sizeof(int32_t)) * (size_t)num_inst;
+}
+
+// The host copies of a batch's graph and instance tables (hi: inst_bytes).
 static void fill_tables(const sssp_csr *graphs, int32_t num_graphs, const int32_t *inst_graph,
                         const int32_t *inst_source, int32_t num_inst, GraphDev *hg,
                         InstDev *hi) {
@@ -897,6 +902,16 @@ static void fill_tables(const sssp_csr *graphs, int32_t num_graphs, const int32_
     hi[i].n = graphs[inst_graph[i]].n;
     base += hi[i].n;
   }
+  // the order: eight size classes an octave, each in instance order
+  const auto size_class = [](int32_t n) {
+    const int top = 31 - __builtin_clz((unsigned)n | 8u);
+    return 255 - (8 * top + ((n >> (top - 3)) & 7));
+  };
+  int32_t at[257] = {};
+  for (int32_t i = 0; i < num_inst; ++i) at[size_class(hi[i].n) + 1]++;
+  for (int k = 0; k < 256; ++k) at[k + 1] += at[k];
+  int32_t *order = (int32_t *)(hi + num_inst);
+  for (int32_t i = 0; i < num_inst; ++i) order[at[size_class(hi[i].n)]++] = i;
 }
 
 // Round arguments and state buffers of a batch (the tables a.graphs and
@@ -926,7 +941,7 @@ static sssp_status batch_args(DevWS &ws, const sssp_csr *graphs, int32_t num_gra
   GraphDev *dg;
   InstDev *di;
   if ((s = ws_arr(ws, S_GTAB, (size_t)num_graphs, &dg))) return s;
-  if ((s = ws_arr(ws, S_ITAB, (size_t)num_inst, &di))) return s;
+  if ((s = ws_get(ws, S_ITAB, inst_bytes(num_inst), (void **)&di))) return s;
   a.graphs = dg;
   a.insts = di;
   if (stats) {
@@ -1059,7 +1074,7 @@ sssp_status sssp_solve_batch(const sssp_csr *graphs, int32_t num_graphs,
   if ((s = batch_args(ws, graphs, num_graphs, inst_graph, num_inst, total, max_n, cost, pred,
                       stats != nullptr, a)))
     return s;
-  const size_t tab_bytes = sizeof(GraphDev) * num_graphs + sizeof(InstDev) * num_inst;
+  const size_t tab_bytes = sizeof(GraphDev) * num_graphs + inst_bytes(num_inst);
   void *hp;
   if ((s = pinned_get(ws, tab_bytes, &hp))) return s;
   GraphDev *hg = (GraphDev *)hp;
@@ -1072,7 +1087,7 @@ sssp_status sssp_solve_batch(const sssp_csr *graphs, int32_t num_graphs,
   HIPCHK(hipStreamWaitEvent(stream, ws.last, 0));
   HIPCHK(hipMemcpyAsync((void *)a.graphs, hg, sizeof(GraphDev) * num_graphs,
                         hipMemcpyHostToDevice, stream));
-  HIPCHK(hipMemcpyAsync((void *)a.insts, hi, sizeof(InstDev) * num_inst, hipMemcpyHostToDevice,
+  HIPCHK(hipMemcpyAsync((void *)a.insts, hi, inst_bytes(num_inst), hipMemcpyHostToDevice,
                         stream));
   HIPCHK(hipEventRecord(ws.staged, stream));
   KernelTimer tm;
@@ -1198,16 +1213,16 @@ static sssp_status plan_build(const sssp_csr *graphs, int32_t num_graphs,
   p->f32 = graphs[0].dtype == SSSP_F32;
   p->max_n = max_n;
   std::vector<GraphDev> hg((size_t)num_graphs);
-  std::vector<InstDev> hi((size_t)num_inst);
-  fill_tables(graphs, num_graphs, inst_graph, inst_source, num_inst, hg.data(), hi.data());
+  std::vector<int32_t> htab(inst_bytes(num_inst) / sizeof(int32_t));
+  InstDev *hi = (InstDev *)htab.data();
+  fill_tables(graphs, num_graphs, inst_graph, inst_source, num_inst, hg.data(), hi);
   if (kind == SSSP_PLAN_BATCH) {
     if ((s = batch_args(p->ws, graphs, num_graphs, inst_graph, num_inst, total, max_n, cost,
                         pred, p->with_stats, p->a)))
       return s;
     HIPCHK(hipMemcpy((void *)p->a.graphs, hg.data(), sizeof(GraphDev) * num_graphs,
                      hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy((void *)p->a.insts, hi.data(), sizeof(InstDev) * num_inst,
-                     hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy((void *)p->a.insts, hi, inst_bytes(num_inst), hipMemcpyHostToDevice));
     p->batch_pred = pred;
     p->low_spread = all_low_spread(graphs, inst_graph, num_inst);
   } else {

@@ -7,7 +7,9 @@
 // tails' C are gathered, and there is no list but the relax set, which stays
 // in the workgroup's LDS.  D and C of a solve fit the XCD's L2; a batch runs
 // its instances one after another on each team, so their working sets stay
-// there too instead of sweeping all instances every round.  A single large
+// there too instead of sweeping all instances every round (the large ones
+// first: 240 graphs of 300 to 700 vertices and one of 200000 take 2.1 ms wherever
+// it stands among them; last in the queue it took 3.5).  A single large
 // solve takes all XCDs as one team.
 //
 // What bounds it: on one XCD the L2's requests (about 16 a cycle) and the
@@ -165,10 +167,11 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
     team_min(fin, d0, d1, false);
     same = eq;
   }
-  int inst = team;
-  while (inst < a.num_inst && !lost) {
-    int32_t sb = 0, gi = 0, src = a.source;
+  int turn = team;  // of the queue, the large instances first
+  while (turn < a.num_inst && !lost) {
+    int32_t sb = 0, gi = 0, src = a.source, inst = 0;
     if constexpr (BATCH) {
+      inst = ((const int32_t *)(a.insts + a.num_inst))[turn];
       const InstDev id = a.insts[inst];
       sb = id.sbase;
       gi = id.graph;
@@ -535,7 +538,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
     }
     __syncthreads();
     // (uniform: the graph's fields then sit in scalar registers)
-    inst = __builtin_amdgcn_readfirstlane(s.next);
+    turn = __builtin_amdgcn_readfirstlane(s.next);
     lost = __builtin_amdgcn_readfirstlane(s.lost) != 0;
     __syncthreads();
   }

@@ -179,6 +179,36 @@ def test_batch_of_one(sp, n, kind, relax):
     sp.check()
 
 
+@pytest.mark.parametrize("where", [0, 33, 69])
+def test_mixed_sizes(sp, where):
+    # a queue of small instances (1 vertex upwards) with a large one among them,
+    # which is taken first wherever it stands
+    rng = np.random.default_rng(where)
+    sizes = [1, 2, 7, 8, 9, 15, 16, 100, 127, 129, 500, 1000, 5000]
+    glist = [rand(rng, n, 6 * n, 40) for n in sizes] + [rand(rng, 70001, 6 * 70001, 40)]
+    graphs = [sp.Graph(g.n, g.src, g.dst, g.w, scope="all") for g in glist]
+    inst = [i % len(sizes) for i in range(69)]
+    inst.insert(where, len(sizes))
+    srcs = [int(rng.integers(0, glist[g].n)) for g in inst]
+    print("dense mixed", where, flush=True)
+    out = []
+    for launch in (None, dict(wg=-1)):
+        sp.set_launch(launch)
+        try:
+            c, p, st = sp.solve_batch(graphs, inst, srcs, with_stats=True)
+            sync()
+        finally:
+            sp.set_launch(None)
+        out.append((to_np(c), to_np(p), st))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    assert out[0][2] == out[1][2]
+    plan = sp.Plan(graphs, inst, srcs, with_stats=True)
+    plan.run()
+    sync()
+    assert np.array_equal(to_np(plan.cost), out[0][0]) and plan.stats() == out[0][2]
+    plan.close()
+
+
 def test_training_step_of_one_source(sp):
     n = 40001
     g = rand(np.random.default_rng(3), n, 8 * n, "f32")
