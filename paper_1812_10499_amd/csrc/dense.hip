@@ -81,10 +81,10 @@ __device__ __forceinline__ T *scalar_ptr(T *p) {
   return (T *)(uintptr_t)readlane64((int64_t)(uintptr_t)p, 0);
 }
 
-// WIDE: one instance, by one team of q.K blocks (up to kMaxWide) over all XCDs.
-// Every wait reads as many words as the widest team of its form has blocks: one
-// a lane here, four where WIDE.  That is the team's width and nothing else: a
-// batch of one instance may be as wide as a single solve.
+// WIDE: the instances one after another, by one team of q.K blocks (up to
+// kMaxWide) over all XCDs.  Every wait reads as many words as the widest team of
+// its form has blocks: one a lane, four where WIDE.  That is the team's width and
+// nothing else: a batch may be as wide as a single solve.
 template <class V, bool BATCH, bool WIDE>
 __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArgs q) {
   __shared__ DenseLds s;
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
         // the words are rewritten by the team's next instance: only after
         // every block has read them
         int32_t z0 = 0, z1 = 0;
-        if (BATCH && !WIDE) team_min(fin, z0, z1, false);
+        if (BATCH) team_min(fin, z0, z1, false);
         break;
       }
       ++bounds;
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
     }
     // ---- the next instance: the team's first block takes it from the queue
     ++ep;
-    if (!BATCH || WIDE) break;
+    if (!BATCH) break;
     if (wv == 0) {
       int32_t next = 0;
       if (j == 0) {
@@ -556,10 +556,13 @@ __global__ void dense_counts_kernel(RoundArgs a) {
     for (int k = 0; k < 4; ++k) a.istat[4 * i + k] = 0;
 }
 
-// From here one instance runs as one team over all XCDs (agent-scope stores,
-// 256 words a barrier), below as one on an XCD: 30000 vertices of degree 8 take
-// 0.30 ms on one, 0.33 on all; 40000 0.38 and 0.37; 150001 0.93 and 0.51.
-constexpr int32_t kWideFrom = 36864;
+// From here one instance, two or three run, one after another, on one team over
+// all XCDs (agent-scope stores, 256 words a barrier), below each on an XCD: one of
+// 30000 vertices of degree 8 takes 0.30 ms on one, 0.33 on all; 40000 0.38 and
+// 0.37; 150001 0.93 and 0.51.  Two of 150000 1.01 and 1.02, 200000 1.30 and 1.19,
+// 10^6 7.6 and 3.7 (7.2 on the grid-wide kernel); three of 300000 1.88 and 2.2,
+// 500000 2.98 and 2.9, 10^6 7.9 and 5.5.
+constexpr int32_t kWideFrom[3] = {36864, 163840, 491520};
 // Blocks per team: one per 1024 vertices where the instances then all run at
 // once; else smaller teams, more of them, down to one block per 8192 vertices
 // (and at most 16 where instances queue): 256 instances of 5 to 6 thousand
@@ -587,7 +590,7 @@ static hipError_t launch_dense_t(const RoundArgs &a, const LaunchGeom &geo, int3
                                  const KernelTimer *timer, Launcher &L, bool *done) {
   *done = false;
   hipError_t e;
-  const bool wide = a.num_inst == 1 && max_n > kWideFrom;
+  const bool wide = a.num_inst <= 3 && max_n > kWideFrom[a.num_inst - 1];
   int occ = 0;
   if ((e = wide ? dense_occupancy<V, BATCH, true>(&occ)
                 : dense_occupancy<V, BATCH, false>(&occ)) != hipSuccess)

@@ -209,6 +209,37 @@ def test_mixed_sizes(sp, where):
     plan.close()
 
 
+@pytest.mark.parametrize("sizes,kind", [((163840, 900), 20), ((163841, 5, 163000), 20),
+                                        ((5, 163841), "f32"), ((7000, 491521, 40000), 9)])
+def test_few_large_instances(sp, sizes, kind):
+    # two or three instances, around the lines from which they share a team over
+    # all XCDs
+    rng = np.random.default_rng(sizes[0])
+    glist = [rand(rng, n, 4 * n, kind) for n in sizes]
+    graphs = [sp.Graph(g.n, g.src, g.dst, g.w, scope="all",
+                       relax=("correcting" if k == 1 else "setting"))
+              for k, g in enumerate(glist)]
+    which, srcs = list(range(len(sizes))), [g.source for g in glist]
+    print("dense few", sizes, kind, flush=True)
+    cost, pred, st = sp.solve_batch(graphs, which, srcs, with_stats=True)
+    sync()
+    bases, _ = sp.batch_layout(graphs, which)
+    plan = sp.Plan(graphs, which, srcs, with_stats=True)
+    for _ in range(2):
+        plan.run()
+        sp.solve(graphs[0], 0)
+        sync()
+        assert torch.equal(plan.cost, cost) and torch.equal(plan.pred, pred)
+        assert plan.stats() == st
+    plan.close()
+    for k, g in enumerate(glist):
+        ref = oracle_solution(g.n, g.src, g.dst, g.w, g.source, "all",
+                              graphs[k].effective_relax, graphs[k].effective_delta)
+        sl = slice(bases[k], bases[k] + g.n)
+        assert_same_solution(cost[sl], pred[sl], st[k], ref, "inst %d" % k)
+    sp.check()
+
+
 def test_training_step_of_one_source(sp):
     n = 40001
     g = rand(np.random.default_rng(3), n, 8 * n, "f32")
