@@ -783,7 +783,10 @@ hipError_t launch_renumber(int32_t n, int32_t m, int32_t dmax, const int32_t *ou
 // position).  Lists are read through the caches; the work is the sum of the
 // squared in-degrees, so it serves graphs whose largest in-degree is at most
 // kRankList (a grid's 4, a random digraph's 30) and replaces the radix
-// passes over the whole weight (four for float32) and the head.
+// passes over the whole weight (four for float32) and the head.  New weights
+// this way and sorted, float32 and (sorted) int32: 0.1 M vertices of in-degree 8
+// 83, 199 and 144 us, 50000 of 64 226 and 417, of 128 559, 801 and 633, 20000 of
+// 256 600, 696 and 539, of 400 1377 and 906.
 // head: by CSC position, or null (then out_dst of the entry's edge id).
 constexpr int32_t kRankList = 128;
 
