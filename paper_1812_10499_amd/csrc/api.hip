@@ -834,7 +834,7 @@ static sssp_status solve_one(const sssp_csr *g, int32_t source, int32_t target, 
   Launcher L;
   L.stream = stream;
   HIPCHK(launch_solve(f32, false, a, pred, geo, nullptr, g->n, timer, L));
-  if ((s = trace_end(a, geo.blocks, stream))) return s;
+  if ((s = trace_end(a, rounds_blocks(false, a, geo), stream))) return s;
   if (stats) {
     void *hp;
     if ((s = pinned_get(ws, sizeof(Ctl), &hp))) return s;
@@ -1096,7 +1096,7 @@ sssp_status sssp_solve_batch(const sssp_csr *graphs, int32_t num_graphs,
   Launcher L;
   L.stream = stream;
   HIPCHK(launch_solve(f32, true, a, pred, geo, a.istat, max_n, timer, L));
-  if ((s = trace_end(a, geo.blocks, stream))) return s;
+  if ((s = trace_end(a, rounds_blocks(true, a, geo), stream))) return s;
   if (stats) s = batch_stats(a, num_inst, stats, stream);
   HIPCHK(hipEventRecord(ws.last, stream));
   return s;

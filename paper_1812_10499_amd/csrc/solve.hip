@@ -1930,6 +1930,16 @@ hipError_t launch_kernel(Launcher &L, const void *fn, dim3 grid, dim3 block, voi
   return hipSuccess;
 }
 
+// A barrier's cache write-backs and invalidations queue up per XCD, so half the
+// blocks make it cheaper, and a graph of moderate size has no use for more: 128
+// against 256 blocks, skewed graphs of 0.13 M edges 424 (439) us, 4.2 M 633 (685),
+// 6.3 M 748 (786), 8.4 M 773 (793) and 960 (960), 16.8 M 1093 (969), 67 M 2919
+// (2132); random, scope OPEN, 4 M 3625 (3863).
+int rounds_blocks(bool batch, const RoundArgs &a, const LaunchGeom &geo) {
+  const bool half = !batch && geo.all_blocks && a.g.m <= kHalfGridEdges && geo.blocks == geo.cus;
+  return half && geo.blocks > 1 ? geo.blocks / 2 : geo.blocks;
+}
+
 template <class V, bool BATCH>
 static hipError_t launch_solve_t(const RoundArgs &a, int32_t *pred, const LaunchGeom &geo,
                                  long long *istat, int32_t max_n, const KernelTimer *timer,
@@ -1976,14 +1986,7 @@ static hipError_t launch_solve_t(const RoundArgs &a, int32_t *pred, const Launch
   }
   if (L.graph) timer = nullptr;
   if (timer && (e = hipEventRecord(timer->start, L.stream)) != hipSuccess) return e;
-  int blocks = geo.blocks;
-  // A barrier's cache write-backs and invalidations queue up per XCD, so half
-  // the blocks make it cheaper, and a graph of moderate size has no use for
-  // more: 128 against 256 blocks, skewed graphs of 0.13 M edges 424 (439) us, 4.2
-  // M 633 (685), 6.3 M 748 (786), 8.4 M 773 (793) and 960 (960), 16.8 M 1093
-  // (969), 67 M 2919 (2132); random, scope OPEN, 4 M 3625 (3863).
-  if (!BATCH && geo.all_blocks && a.g.m <= kHalfGridEdges && blocks == geo.cus) blocks /= 2;
-  if (blocks < 1) blocks = 1;
+  const int blocks = rounds_blocks(BATCH, a, geo);
   if ((e = launch_kernel(L, (const void *)rounds_kernel<V, BATCH>, dim3(blocks), dim3(RBS),
                          params, true)) != hipSuccess)
     return e;

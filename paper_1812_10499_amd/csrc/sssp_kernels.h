@@ -237,6 +237,8 @@ hipError_t launch_pred(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
 hipError_t fault_flag_take(int32_t *out, hipStream_t stream);
 // the flag's address on the current device (looked up once per device)
 hipError_t fault_flag_address(int32_t **out);
+// the blocks of the grid-wide kernel (solve.hip) under this geometry
+int rounds_blocks(bool batch, const RoundArgs &a, const LaunchGeom &geo);
 hipError_t round_kernel_occupancy(bool f32, bool batch, int *blocks_per_cu);
 
 // Bytes of the static scratch region of allocation-free solves, and its
