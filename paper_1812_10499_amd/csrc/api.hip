@@ -455,7 +455,10 @@ sssp_status state_buffers(DevWS &w, int32_t total, int32_t num_inst, bool batch,
 
 // Round trace: with SSSP_TRACE=<path> in the environment, a solve records
 // per-round timestamps and list sizes on the device and, after the kernel,
-// appends them as CSV lines to <path> (synchronizes the stream).
+// appends them as CSV lines to <path> (synchronizes the stream).  The grid-wide
+// kernel records them, which also takes the solves of dense teams while the
+// trace is on; small graphs, and meshes in teams or a workgroup each, record
+// none: their rows are zeros, with a line on stderr.
 constexpr int kTraceRounds = 100000;
 constexpr int kTraceBlkRounds = 64;  // rounds with per-block phase end times
 
@@ -485,6 +488,8 @@ sssp_status trace_end(const RoundArgs &a, int nblocks, hipStream_t stream) {
   const int nr = c.rounds < kTraceRounds ? c.rounds : kTraceRounds;
   std::vector<long long> h((size_t)nr * kTraceFields);
   HIPCHK(hipMemcpy(h.data(), a.trace, h.size() * sizeof(long long), hipMemcpyDeviceToHost));
+  if (nr > 0 && h[TR_START] == 0)
+    fprintf(stderr, "sssp: SSSP_TRACE: this solve's kernel records no rounds\n");
   FILE *f = fopen(path, "a");
   if (!f) return SSSP_ERR_ARG;
   fprintf(f, "round,start,arr_relax,end_relax,arr_fused,end_fused,nf,ef,no,eo,mode,nl\n");

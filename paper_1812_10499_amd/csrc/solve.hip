@@ -1958,7 +1958,7 @@ static hipError_t launch_solve_t(const RoundArgs &a, int32_t *pred, const Launch
       return e;
     return launch_wg(V::INF == KeyF32::INF, BATCH, a, pred, geo, istat, max_n, timer, L, redo);
   }
-  if (a.dense && geo.dense) {
+  if (a.dense && geo.dense && !a.trace) {  // (only the kernel below records a round trace)
     bool done = false;
     if ((e = launch_dense(V::INF == KeyF32::INF, BATCH, a, geo, max_n, timer, L, &done)) !=
         hipSuccess)

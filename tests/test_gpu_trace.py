@@ -17,7 +17,7 @@ def sp():
     return sp
 
 
-@pytest.mark.parametrize("name,blocks", [("skewed", None), ("skewed", 40)])
+@pytest.mark.parametrize("name,blocks", [("random", None), ("skewed", None), ("skewed", 40)])
 def test_trace_rows(sp, tmp_path, monkeypatch, name, blocks):
     g = gen.random_workload(n=9000, m=72000) if name == "random" else gen.rmat_workload(scale=14)
     G = sp.Graph(g.n, g.src, g.dst, g.w)
