@@ -184,7 +184,6 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
       src = __builtin_amdgcn_readfirstlane(src);
       G.n = __builtin_amdgcn_readfirstlane(G.n);
       G.lc = __builtin_amdgcn_readfirstlane(G.lc);
-      G.all = __builtin_amdgcn_readfirstlane(G.all);
       G.delta = __builtin_amdgcn_readfirstlane(G.delta);
       G.out_rec = scalar_ptr(G.out_rec);
       G.vrec = scalar_ptr(G.vrec);
@@ -195,7 +194,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
       G.rank = scalar_ptr(G.rank);
     }
     const int n = G.n;
-    const bool lc = G.lc != 0, all = G.all != 0;
+    const bool lc = G.lc != 0;
     int32_t tgt = BATCH ? -1 : a.target;
     if (G.rank) {
       src = G.rank[src];
@@ -357,8 +356,8 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           dy[u] = (int32_t)(dk[u] >> 32);
-          act[u] = on[u] && c[u] != V::INF && (dy[u] != V::INF || all) && sk[u] < rec[u].y &&
-                   V::add(md, rec[u].w) < dy[u];
+          act[u] = on[u] & (c[u] != V::INF) & (sk[u] < rec[u].y) &
+                   (V::add(md, rec[u].w) < dy[u]);
           cz[u] = ld_relaxed(&Cold[act[u] && sk[u] == 0 ? rec[u].z : 0]);
         }
 #pragma unroll
@@ -419,7 +418,6 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
           if (!on[u]) continue;
           const int32_t deg = rec[u].y;
           const bool disc = dy[u] != V::INF;
-          if (!disc && !all) continue;
           if (sk[u] != sk0[u]) SK[y[u]] = sk[u];
           nscan += (unsigned long long)deg;
           if (c[u] == V::INF) {  // unreachable: C = INF in both buffers now
