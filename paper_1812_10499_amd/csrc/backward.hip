@@ -146,7 +146,7 @@ __global__ __launch_bounds__(BBS) void bw_parent_kernel(BackArgs a) {
 // Vertices to start from, over the whole chip: wave wid of `waves` takes every
 // waves-th chunk of [at, end).
 struct SweepSource {
-  static constexpr int kScope = __HIP_MEMORY_SCOPE_AGENT;
+  static constexpr bool kOneL2 = false;
   int64_t at, end, step;
   __device__ __forceinline__ bool grab(const BackArgs &, int64_t *pos, int64_t *lim) {
     if (at >= end) return false;
@@ -161,12 +161,13 @@ struct SweepSource {
 // instance it is at (plus one) and the chunks of it that are taken; the wave
 // that finds the last one taken claims the next instance.
 struct XcdSource {
-  static constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
+  static constexpr bool kOneL2 = true;
   unsigned long long *cur;
   unsigned int *queue;
   __device__ __forceinline__ bool grab(const BackArgs &a, int64_t *pos, int64_t *lim) {
     unsigned long long t = 0;
-    if (lane_id() == 0) t = __hip_atomic_fetch_add(cur, 1ull, __ATOMIC_RELAXED, kScope);
+    if (lane_id() == 0)
+      t = __hip_atomic_fetch_add(cur, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int32_t ins = __builtin_amdgcn_readfirstlane((int)(t >> 32)) - 1;
     int32_t c = __builtin_amdgcn_readfirstlane((int)t);
     if (ins == -2) return false;
@@ -193,7 +194,6 @@ struct XcdSource {
 // Returns the number of vertices this lane completed.
 template <typename SOURCE>
 __device__ __forceinline__ int32_t walk(const BackArgs &a, SOURCE source) {
-  constexpr int SCOPE = SOURCE::kScope;
   const int l = lane_id();
   int64_t pos = 0, lim = 0;
   bool more = true;
@@ -241,7 +241,7 @@ __device__ __forceinline__ int32_t walk(const BackArgs &a, SOURCE source) {
           w = __hip_atomic_exchange(&a.word[p],
                                     ((unsigned long long)(0x80000000u | (uint32_t)e) << 32) |
                                         (unsigned long long)__float_as_uint(acc),
-                                    __ATOMIC_RELAXED, SCOPE);
+                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if ((long long)w < 0) {
           const int32_t e2 = (int32_t)((uint32_t)(w >> 32) & 0x7fffffffu);
           const float s = __uint_as_float((uint32_t)w);
@@ -252,9 +252,10 @@ __device__ __forceinline__ int32_t walk(const BackArgs &a, SOURCE source) {
           act = false;
         }
       } else {
-        __hip_atomic_store(&a.acc[v], acc, __ATOMIC_RELAXED, SCOPE);
+        put((int32_t *)&a.acc[v], __float_as_int(acc), SOURCE::kOneL2);
         stores_done();
-        w = __hip_atomic_fetch_add(&a.word[p], 1ull << 32, __ATOMIC_RELAXED, SCOPE);
+        w = __hip_atomic_fetch_add(&a.word[p], 1ull << 32, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("" ::: "memory");  // nothing below is read before the count
         if ((uint32_t)(w >> 32) + 1u == (uint32_t)w) many = true;
         else act = false;

@@ -16,6 +16,14 @@ constexpr int kSpinLimit = 1 << 24;
 // reach the shared L2 (about 440 cycles until done, against 830 for an
 // agent-scope store; with the latter a 1024 x 1024 grid takes 45 ms in a team
 // of 64 waves, 22.4 without).
+// same_l2 is narrower than the sharing: HIP promises a workgroup-scope store to
+// the workgroup alone.  Relied on is its form on gfx950, a store with sc0 and
+// not sc1 (a CPU test reads it from the compiler's output): the L1 writes every
+// store through, so that once vmcnt has counted it (stores_done) it lies in the
+// L2 of the XCD, where the agent-scope loads of that XCD's other workgroups look.
+// That they are on that XCD is established by xcd_id() when a team starts.
+// Read-modify-writes need nothing of the kind: they are at agent scope, where
+// the instruction is the same.
 __device__ __forceinline__ void put(int32_t *p, int32_t v, bool same_l2) {
   if (same_l2) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
