@@ -34,6 +34,9 @@
  *    queued.  No C++ exception crosses this boundary.
  *  - The library keeps a per-device workspace cache (allocated with
  *    hipMalloc on first use or growth, freed by sssp_release_workspace).
+ *    A build or new weights take 20 bytes an edge of it (16 a vertex, and 4
+ *    an edge, where there are more vertices than edges), at most two more for
+ *    digit counts, and use parts of the graph's buffer as scratch meanwhile.
  *    Concurrent calls on one device from several host threads are
  *    serialized by the library.
  */

@@ -22,7 +22,7 @@ enum Slot {
   S_C, S_C1, S_ARRIVE, S_MTMP, S_OV0, S_OP0, S_OI0, S_OV1, S_OP1, S_OI1, S_FV, S_FP, S_FI, S_CTL,
   S_IMIN, S_ITHR, S_IROUNDS, S_ISCAN, S_DEGEN, S_LVL, S_FLAG, S_SPRED, S_ISTAT,
   S_GTAB, S_ITAB,
-  S_BK_COLS, S_BK_HIST, S_BK_TAIL, S_BK_HEAD, S_BK_DEG, S_BK_STATUS,
+  S_BK_COLS, S_BK_HIST, S_BK_HEAD, S_BK_STATUS,
   S_BW_ACC, S_BW_PAR, S_BW_WORD, S_BW_CTL, S_BW_TAB,
   S_TRACE, S_FLAGS, S_PART, S_D64, S_FX, S_OX0, S_OX1, S_LV0, S_LV1, S_DR, S_INSTOF, S_IDEAD,
   NSLOTS
@@ -343,20 +343,27 @@ SolverCopy solver_copy(const sssp_csr *g) {
   return c;
 }
 
-// Sort temporaries of the builder for n vertices and m edges.
-sssp_status build_temps(DevWS &ws, int32_t n, int32_t m, BuildTemps *t) {
+// Sort temporaries of the builder for n vertices and m edges.  Half of the eight
+// sort columns, the tails and the degrees lie in arrays of the graph itself that
+// are written last, from the finished lists: the out-edge records (vertex records
+// where there are more vertices than edges), the (tail, weight) pairs and the
+// in-side records.  The workspace holds the rest, 20 bytes an edge.
+sssp_status build_temps(DevWS &ws, int32_t n, int32_t m, int32_t *out_rec, int32_t *vrec,
+                        int32_t *vin, int32_t *in_sw, BuildTemps *t) {
   sssp_status s;
-  // eight sort columns; their starts keep the allocation's alignment
-  const size_t M = (((size_t)(m > n ? m : n) + 63) & ~(size_t)63);
+  const size_t most = (size_t)(m > n ? m : n);
+  // (the starts keep the allocation's alignment)
+  const size_t M = (most + 63) & ~(size_t)63;
   int32_t *cols;
-  if ((s = ws_arr(ws, S_BK_COLS, 8 * M, &cols))) return s;
+  if ((s = ws_arr(ws, S_BK_COLS, 4 * M, &cols))) return s;
+  int32_t *const last = m >= n ? out_rec : vrec;
   for (int k = 0; k < 4; ++k) {
-    t->a[k] = cols + (size_t)k * M;
-    t->b[k] = cols + (size_t)(4 + k) * M;
+    t->a[k] = last + (size_t)k * most;
+    t->b[k] = cols + (size_t)k * M;
   }
-  if ((s = ws_arr(ws, S_BK_TAIL, (size_t)(m > 0 ? m : 1), &t->tail))) return s;
+  t->tail = in_sw;
+  t->deg = vin;
   if ((s = ws_arr(ws, S_BK_HEAD, (size_t)(m > 0 ? m : 1), &t->head))) return s;
-  if ((s = ws_arr(ws, S_BK_DEG, (size_t)n, &t->deg))) return s;
   if ((s = ws_arr(ws, S_BK_HIST, build_hist_entries(n, m), &t->hist))) return s;
   if ((s = ws_arr(ws, S_BK_STATUS, kBuildStatus, &t->status))) return s;
   return SSSP_OK;
@@ -630,7 +637,9 @@ sssp_status sssp_build_csr(int32_t n, int32_t m, sssp_dtype dtype, sssp_order or
   int32_t *in_off = arr(B_IN_OFF), *in_src = arr(B_IN_SRC), *in_eid = arr(B_IN_EID);
   int32_t *in_w = arr(B_IN_W), *out_wmin = arr(B_OUT_WMIN);
   BuildTemps t;
-  if ((s = build_temps(ws, n, m, &t))) return s;
+  if ((s = build_temps(ws, n, m, arr(B_S_OUT_REC), arr(B_S_VREC), arr(B_S_VIN), arr(B_S_IN_SW),
+                       &t)))
+    return s;
   void *hp;
   if ((s = pinned_get(ws, kBuildStatus * sizeof(int32_t), &hp))) return s;
   const int32_t *hs = (const int32_t *)hp;
@@ -744,7 +753,8 @@ sssp_status sssp_set_weights(sssp_csr *g, const void *w, void *stream_) {
   DevWS &ws = *wp;
   HIPCHK(hipStreamWaitEvent(stream, ws.last, 0));
   BuildTemps t;
-  if ((s = build_temps(ws, g->n, g->m, &t))) return s;
+  const SolverCopy c = solver_copy(g);
+  if ((s = build_temps(ws, g->n, g->m, c.out_rec, c.vrec, c.vin, c.in_sw, &t))) return s;
   // validate before anything is written: on error the graph is unchanged
   void *hp;
   if ((s = pinned_get(ws, kBuildStatus * sizeof(int32_t), &hp))) return s;
@@ -765,7 +775,6 @@ sssp_status sssp_set_weights(sssp_csr *g, const void *w, void *stream_) {
     HIPCHK(hipEventRecord(ws.last, stream));
     return SSSP_ERR_OVERFLOW;
   }
-  const SolverCopy c = solver_copy(g);
   HIPCHK(launch_set_weights(g->n, g->m, f32, g->deg_max, (const int32_t *)w, g->out_off,
                             g->in_eid, (int32_t *)g->out_w, (int32_t *)g->in_w,
                             (int32_t *)g->out_wmin, c, stream));

@@ -212,10 +212,9 @@ static inline int64_t sort_tiles(int32_t m) {
 }
 
 size_t build_hist_entries(int32_t n, int32_t m) {
-  const int32_t big = m > n ? m : n;
-  // (a large m has fewer, larger tiles than a smaller n may have)
-  size_t t = (size_t)sort_tiles(big > 0 ? big : 1);
-  if (t < kBigSort / (4 * kSortThreads)) t = kBigSort / (4 * kSortThreads);
+  // rows of m edges or n vertices (a large m may have fewer, larger tiles)
+  const size_t tm = (size_t)sort_tiles(m > 0 ? m : 1), tn = (size_t)sort_tiles(n > 0 ? n : 1);
+  const size_t t = tm > tn ? tm : tn;
   const size_t sums = ((size_t)n + 1 + SCAN_TILE - 1) / SCAN_TILE + 64;
   return (t + 1) * (1u << kMaxDigit) + sums;
 }

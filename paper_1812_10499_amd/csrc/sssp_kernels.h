@@ -270,7 +270,10 @@ hipError_t launch_small(bool f32, bool batch, const RoundArgs &a, int32_t *pred,
 
 // ------------------------------------------------------------- builder
 struct BuildTemps {
-  int32_t *a[4], *b[4];  // sort columns, max(m, n) each
+  // Sort columns, max(m, n) each.  a lies in the graph's out_rec (m >= n) or vrec,
+  // tail in its in_sw, deg in its vin: nothing may write those arrays before the
+  // last use of these.
+  int32_t *a[4], *b[4];
   int32_t *hist;         // digit counts per tile (build_hist_entries)
   int32_t *tail;         // m: tails (by edge id, or by position in the copy's CSR)
   int32_t *head;         // m: heads by CSC position

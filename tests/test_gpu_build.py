@@ -80,3 +80,33 @@ def test_bad_edges_and_weights_refused(sp):
         G.set_weights(torch.tensor([1, -2, 3], dtype=torch.int32))
     sync()
     assert np.array_equal(to_np(G.arrays()["out_w"]), w)
+
+
+@pytest.mark.parametrize("n,m", [(1000, 8000), (1000000, 8000001), (6000001, 900)])
+def test_workspace(sp, n, m):
+    # what a build and new weights take of the device beside the graph's own
+    # buffer, from an empty workspace: 20 bytes an edge (16 a vertex where there
+    # are more vertices), the digit counts and an eighth of headroom
+    g = torch.Generator(device="cuda").manual_seed(n)
+    src, dst = (torch.randint(0, n, (m,), generator=g, device="cuda", dtype=torch.int32)
+                for _ in range(2))
+    w = torch.rand(m, generator=g, device="cuda") + 0.5
+    G = sp.Graph(n, src, dst, w, order="degree")  # (code objects, the allocator's pool)
+    we = G.to_edge_order(w)
+    want = {k: v.clone() for k, v in G.solver_arrays().items()}
+    sync()
+    sp.sssp_release_workspace()
+    free = torch.cuda.mem_get_info()[0]
+    held = torch.cuda.memory_reserved()
+    del G
+    G = sp.Graph(n, src, dst, w, order="degree")
+    G.set_weights(we)
+    sync()
+    assert torch.cuda.memory_reserved() == held  # (the graph's buffer is the old one's)
+    taken = free - torch.cuda.mem_get_info()[0]
+    counts = (max(m, n) // 4096 + 2) * 2048 * 4
+    most = 1.13 * (16 * max(m, n) + 4 * m + counts)
+    print("workspace", n, m, taken, int(most), flush=True)
+    assert taken <= most + (8 << 20)  # (allocations are whole pages of 2 MiB)
+    for k, v in G.solver_arrays().items():
+        assert torch.equal(v, want[k]), k
