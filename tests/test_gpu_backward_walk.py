@@ -139,3 +139,37 @@ def test_walk_shared_by_an_xcds_waves(sp, count):
     p = torch.from_numpy(pred).cuda().repeat(count)
     got = sp.backward([G], [0] * count, [root] * count, p, torch.from_numpy(gc).cuda().repeat(count))
     assert np.array_equal(got.cpu().numpy(), count * one)
+
+
+def test_walk_on_xcds_matches_the_sweep(sp):
+    """Instances of different sizes, roots, parents (some spoiled) and gradients,
+    each on one XCD, against the same instances graph by graph, whose totals
+    take the other walk (checked against ordered sums above)."""
+    rng = np.random.default_rng(17)
+    graphs = []
+    for n, k in ((1, 0), (2, 5), (63, 300), (64, 200), (65, 400), (4097, 9000), (30011, 90000),
+                 (60001, 200000)):
+        src, dst = rng.integers(0, n, (2, k)).astype(np.int32)
+        graphs.append(sp.Graph(n, src, dst, (0.5 + rng.random(k)).astype(np.float32)))
+    inst = np.repeat(np.arange(8), [30, 30, 60, 60, 60, 150, 62, 33])
+    rng.shuffle(inst)
+    sources = [int(rng.integers(0, graphs[g].n)) for g in inst]
+    sizes = np.array([graphs[g].n for g in inst])
+    total = int(sizes.sum())
+    assert total >= 1 << 22 and 16 * sizes.max() <= total
+    _, pred, _ = sp.solve_batch(graphs, inst.tolist(), sources)
+    bases = np.concatenate([[0], np.cumsum(sizes)])
+    for i in range(0, len(inst), 40):  # any edge of the graph, mostly another vertex's
+        g = graphs[inst[i]]
+        at = torch.from_numpy(bases[i] + rng.integers(0, g.n, 1 + g.n // 50)).cuda()
+        pred[at] = torch.from_numpy(rng.integers(-1, g.m + 1, len(at)).astype(np.int32)).cuda()
+    gc = torch.randn(total, device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    got = sp.backward(graphs, inst.tolist(), sources, pred, gc)
+    part = 0
+    for k, g in enumerate(graphs):
+        mine = np.nonzero(inst == k)[0]
+        cut = torch.cat([torch.arange(bases[i], bases[i + 1]) for i in mine]).cuda()
+        assert len(cut) < 1 << 22
+        want = sp.backward([g], [0] * len(mine), [sources[i] for i in mine], pred[cut], gc[cut])
+        assert torch.equal(got[part:part + g.m], want), (k, g.n)
+        part += g.m
