@@ -41,7 +41,7 @@ struct SmallLds {
   uint16_t F[N];            // relax set
   uint16_t L[N];            // its members with long out-lists, the huge ones from the end
   int32_t red[2][2 * NW];   // by round parity
-  int32_t nF, nL, nH, target_hit, ndegen;
+  int32_t nF, nL, target_hit, ndegen;  // nL: of the long lists, and (<< 16) the huge ones
   unsigned long long relaxed, scanned, visits, settled;
 };
 
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
     s.off[n] = G.out_off[n];
     s.F[0] = (uint16_t)src;
     s.nF = 1;
-    s.nL = s.nH = 0;
+    s.nL = 0;
     s.ndegen = 0;
     s.target_hit = (tgt >= 0 && tgt == src) ? 1 : 0;
     s.relaxed = s.scanned = s.visits = 0ull;
@@ -207,8 +207,11 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
             dx[u] = s.DR[x];
             if (l == 0) {
               nrel += (unsigned long long)(e[u] - b[u]);
-              if (e[u] - b[u] > kHugeOut) s.L[N - 1 - atomicAdd(&s.nH, 1)] = (uint16_t)x;
-              else if (e[u] - b[u] > kLongOut) s.L[atomicAdd(&s.nL, 1)] = (uint16_t)x;
+              if (__builtin_expect(e[u] - b[u] > kLongOut, 0)) {
+                const bool huge = e[u] - b[u] > kHugeOut;
+                const int at = atomicAdd(&s.nL, huge ? 1 << 16 : 1);
+                s.L[huge ? N - 1 - (at >> 16) : at & 0xffff] = (uint16_t)x;
+              }
             }
             if (e[u] - b[u] > kLongOut) e[u] = b[u];
           }
@@ -226,9 +229,10 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
       }
     }
     __syncthreads();
-    const int nL = s.nL, nH = s.nH;
-    if (nL + nH > 0) {
+    const int lists = s.nL;
+    if (__builtin_expect(lists > 0, 0)) {
       constexpr int U = 4;
+      const int nL = lists & 0xffff, nH = lists >> 16;
       for (int i = tid / SSSP_WAVE; i < nL; i += NW) {
         const int x = s.L[i];
         const int4 *rec = G.out_rec + s.off[x];
@@ -288,7 +292,7 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
       }
     }
     if (md == V::INF) break;  // (A) left nothing open
-    if (tid == 0) s.nL = s.nH = 0;
+    if (tid == 0) s.nL = 0;
     // (C) lower bounds (Eq. 1), Jacobi over C[cur]; SP_4's scope also
     // raises C of undiscovered vertices (an unreachable one, C = INF, keeps
     // it).  In-lists ascend by weight and every term max(C[v], minD) + w is
