@@ -916,10 +916,12 @@ static void fill_tables(const sssp_csr *graphs, int32_t num_graphs, const int32_
     hi[i].n = graphs[inst_graph[i]].n;
     base += hi[i].n;
   }
-  // the order: eight size classes an octave, each in instance order
-  const auto size_class = [](int32_t n) {
+  // the order: first those with at least a 64th of all the vertices, eight size
+  // classes an octave, each in instance order; then the others as they stand
+  const auto size_class = [base](int32_t n) {
+    if (64 * (int64_t)n < base) return 255;
     const int top = 31 - __builtin_clz((unsigned)n | 8u);
-    return 255 - (8 * top + ((n >> (top - 3)) & 7));
+    return 247 - (8 * top + ((n >> (top - 3)) & 7));
   };
   int32_t at[257] = {};
   for (int32_t i = 0; i < num_inst; ++i) at[size_class(hi[i].n) + 1]++;

@@ -7,9 +7,11 @@
 // tails' C are gathered, and there is no list but the relax set, which stays
 // in the workgroup's LDS.  D and C of a solve fit the XCD's L2; a batch runs
 // its instances one after another on each team, so their working sets stay
-// there too instead of sweeping all instances every round (the large ones
-// first: 240 graphs of 300 to 700 vertices and one of 200000 take 2.1 ms wherever
-// it stands among them; last in the queue it took 3.5).  A single large
+// there too instead of sweeping all instances every round (those that make up
+// much of the batch first: 240 graphs of 300 to 700 vertices and one of 200000
+// take 2.1 ms wherever it stands among them; last in the queue it took 3.5.  All by
+// size, 256 graphs of 1 to 200 thousand vertices take 23.4 ms, 22.9 as they come:
+// the largest then contend for memory).  A single large
 // solve takes all XCDs as one team.
 //
 // What bounds it: on one XCD the L2's requests (about 16 a cycle) and the
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
     team_min(fin, d0, d1, false);
     same = eq;
   }
-  int turn = team;  // of the queue, the large instances first
+  int turn = team;  // in the batch's order
   while (turn < a.num_inst && !lost) {
     int32_t sb = 0, gi = 0, src = a.source, inst = 0;
     if constexpr (BATCH) {

@@ -70,8 +70,8 @@ struct GraphDev {
 
 // Instance i of a batch: graph index, source vertex (graph-local), base of
 // its entries in the state arrays, vertex count.  A batch's table is followed
-// by its instances in the order in which queues of them are worked off: the
-// large ones first, by about an eighth of their size.
+// by its instances in the order in which queues of them are worked off: those
+// that make up much of the batch first, by size.
 struct InstDev {
   int32_t graph, source, sbase, n;
 };
