@@ -25,8 +25,10 @@ constexpr int kRegEdges = 4;   // a vertex's lightest in-edges kept in registers
 constexpr int kItemLanes = 8;  // lanes that share a relax item's out-list
 // Longer out-lists are relaxed by a wave each, these by the whole block.  All
 // of them one after another by the whole block, 4096 vertices of degree 64,
-// 256 and 1000 take 1766, 4852 and 4493 us, this way 542, 805 and 2478.  The
-// line at 32 or 16: 212 and 230 us at degree 32 (180 at 64), 500 at degree 64.
+// 256 and 1000 take 1766, 4852 and 4493 us, this way 542, 1021 and 2913 (with four
+// reads in flight a lane instead of two 542, 805 and 2478, but then solves without
+// such lists take 1 % longer).  The line at 32 or 16: 212 and 230 us at degree 32
+// (174 at 64), 500 at degree 64.
 constexpr int32_t kLongOut = 64, kHugeOut = 1024;
 
 // The open set O is implicit: y is open iff it is discovered (D < INF) and
@@ -231,7 +233,7 @@ __global__ __launch_bounds__(T) void small_rounds_kernel(RoundArgs a, int32_t *p
     __syncthreads();
     const int lists = s.nL;
     if (__builtin_expect(lists > 0, 0)) {
-      constexpr int U = 4;
+      constexpr int U = 2;
       const int nL = lists & 0xffff, nH = lists >> 16;
       for (int i = tid / SSSP_WAVE; i < nL; i += NW) {
         const int x = s.L[i];

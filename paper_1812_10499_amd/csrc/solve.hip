@@ -1947,8 +1947,8 @@ static hipError_t launch_solve_t(const RoundArgs &a, int32_t *pred, const Launch
   hipError_t e;
   if (geo.blocks > kMaxBlocks) return hipErrorInvalidConfiguration;
   // (batches too, however few the instances and many the edges: one instance
-  // of 4096 vertices of degree 16, 64, 256 takes 0.18, 0.56, 0.78 ms in its
-  // workgroup, 0.91, 1.69, 5.5 on the grid; four of degree 1000 2.5 and 15.9)
+  // of 4096 vertices of degree 16, 64, 256 takes 0.18, 0.56, 0.99 ms in its
+  // workgroup, 0.91, 1.69, 5.5 on the grid; four of degree 1000 2.9 and 15.9)
   if (max_n <= geo.small_n)
     return launch_small(V::INF == KeyF32::INF, BATCH, a, pred, max_n, timer, L);
   if (geo.wg && !a.scope_all) {
