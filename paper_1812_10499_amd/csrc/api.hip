@@ -807,6 +807,7 @@ static void single_fill(const sssp_csr *g, int32_t source, int32_t target, void 
   a.any_lc = a.g.lc;
   a.dense = dense_graph(g) ? 1 : 0;
   a.mesh = mesh_class(g);
+  a.hub = 64 * (int64_t)g->deg_max >= g->n ? 1 : 0;
 }
 
 static sssp_status single_args(DevWS &ws, const sssp_csr *g, int32_t source, int32_t target,
@@ -1267,6 +1268,7 @@ static sssp_status plan_build(const sssp_csr *graphs, int32_t num_graphs,
       a.any_lc = a.g.lc;
       a.dense = dense_graph(g) ? 1 : 0;
       a.mesh = mesh_class(g);
+      a.hub = 64 * (int64_t)g->deg_max >= g->n ? 1 : 0;
       a.ctl = ctls + i;
       p->seq.push_back(a);
       p->seq_n.push_back(g->n);

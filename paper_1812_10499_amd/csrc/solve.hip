@@ -47,7 +47,8 @@
 namespace sssp {
 
 constexpr int RBS = kRoundBlock;  // threads per block of the round kernel
-constexpr int32_t kHalfGridEdges = 6 << 20;  // single solves up to here: half the grid
+// single solves up to here: half the grid (rounds_blocks)
+constexpr int32_t kHalfGridEdges = 6 << 20, kHalfGridVertices = 5 << 16;
 constexpr int EPT = 4;            // edges per thread per sub-chunk
 constexpr int WIN = RBS;          // list items per window
 // relax: block staging capacity of first discoveries (what does not fit
@@ -1934,9 +1935,14 @@ hipError_t launch_kernel(Launcher &L, const void *fn, dim3 grid, dim3 block, voi
 // blocks make it cheaper, and a graph of moderate size has no use for more: 128
 // against 256 blocks, skewed graphs of 0.13 M edges 424 (439) us, 4.2 M 633 (685),
 // 6.3 M 748 (786), 8.4 M 773 (793) and 960 (960), 16.8 M 1093 (969), 67 M 2919
-// (2132); random, scope OPEN, 4 M 3625 (3863).
+// (2132); random, scope OPEN, 4 M 3625 (3863).  Under scope ALL a large graph
+// without a hub that reaches much of it keeps most of its vertices live for many
+// rounds, and they want the whole chip: degree 12 and a few vertices of 1000 edges,
+// 0.3 M vertices 1763 (1753), degree 8, 0.6 M 2407 (2247), degree 6, 1 M 3256 (2823).
 int rounds_blocks(bool batch, const RoundArgs &a, const LaunchGeom &geo) {
-  const bool half = !batch && geo.all_blocks && a.g.m <= kHalfGridEdges && geo.blocks == geo.cus;
+  const bool small = a.g.m <= kHalfGridEdges &&
+                     (!a.scope_all || a.hub || a.g.n <= kHalfGridVertices);
+  const bool half = !batch && geo.all_blocks && small && geo.blocks == geo.cus;
   return half && geo.blocks > 1 ? geo.blocks / 2 : geo.blocks;
 }
 

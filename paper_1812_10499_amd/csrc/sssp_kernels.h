@@ -147,6 +147,7 @@ struct RoundArgs {
   // kDenseDegree edges (read by the host's choice of kernel)
   int32_t dense;
   int32_t mesh;  // scope OPEN: what the solve's graphs are to teams (MeshClass)
+  int32_t hub;   // single solve: some vertex has edges for a 64th of the vertices
 };
 
 // From vertices of more edges on, one thread's scan of such an in-list and eight
