@@ -173,3 +173,27 @@ def test_walk_on_xcds_matches_the_sweep(sp):
         want = sp.backward([g], [0] * len(mine), [sources[i] for i in mine], pred[cut], gc[cut])
         assert torch.equal(got[part:part + g.m], want), (k, g.n)
         part += g.m
+
+
+@pytest.mark.parametrize("count", [7, 8, 9, 255, 256, 257, 513])
+def test_gradient_over_many_instances(sp, count):
+    """Around the instances that the gradient pass reads together and those it
+    keeps the places of, vertices of few and of many in-edges."""
+    rng = np.random.default_rng(count)
+    n = 37
+    src, dst, root = random_tree(rng, n, "star")
+    G = sp.Graph(n, src, dst, rng.integers(1, 9, len(src)).astype(np.float32))
+    arr = G.arrays()
+    off, hd = arr["out_off"].cpu().numpy(), arr["out_dst"].cpu().numpy()
+    want, preds, gcosts, sources = np.zeros(G.m, np.float32), [], [], []
+    for i in range(count):
+        r = root if i % 3 else int(rng.integers(0, n))
+        pred = tree_pred(rng, n, off, hd, r, i % 5 == 0)
+        gc = rng.standard_normal(n).astype(np.float32)
+        tree_grad(n, off, hd, r, pred, gc, want)
+        sources.append(r)
+        preds.append(pred)
+        gcosts.append(gc)
+    got = sp.backward([G], [0] * count, sources, torch.from_numpy(np.concatenate(preds)).cuda(),
+                      torch.from_numpy(np.concatenate(gcosts)).cuda())
+    assert np.array_equal(got.cpu().numpy(), want)
