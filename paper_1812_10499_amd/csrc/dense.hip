@@ -14,13 +14,14 @@
 // the largest then contend for memory).  A single large
 // solve takes all XCDs as one team.
 //
-// What bounds it: on one XCD the L2's requests (about 16 a cycle) and the
-// compute units' gathers, in the bound step: 21 of 33 us a round at 150001
-// vertices of degree 8; on all XCDs that step takes 4 of 16 us and the two
-// barriers (9.3 and 11 thousand cycles with the wait for the slowest block)
-// most of the rest.  Against the grid-wide kernel: 150001 vertices 1.70 -> 0.51
-// ms, 400003 x 6 2.24 -> 0.81, 10^6 x 8 3.62 -> 1.85, 5000 0.84 -> 0.19; 256
-// graphs of up to 200000 vertices 58.6 -> 23.1 ms; 16 sources on 30011
+// What bounds it: on one XCD the gathers of the bound step, 52 of 81 thousand
+// cycles a round at 150001 vertices of degree 8 (eight such solves: 0.49 M L2
+// requests a round and XCD, reads of 455 cycles against 234 in the mesh kernel,
+// 70 % of them hits; waves wait 75 % of their time and issue 13 %); on all XCDs the
+// step takes 9 of 35 thousand and the two barriers, with the wait for the slowest
+// block, 8 and 11.  Against the grid-wide kernel: 150001 vertices 1.70 -> 0.51
+// ms, 400003 x 6 2.24 -> 0.81, 10^6 x 8 3.62 -> 1.83, 5000 0.84 -> 0.19; 256
+// graphs of up to 200000 vertices 58.6 -> 22.9 ms; 16 sources on 30011
 // vertices 2.53 -> 0.46.
 //
 // A round: relax the block's relax set (returning atomics: the offers to minD
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(DBS) void dense_rounds_kernel(RoundArgs a, DenseArg
         // The scan starts behind the lightest in-edges whose tails are known
         // to be fixed (or unreachable), for good: an open vertex's tails are
         // mostly fixed ones, and reading them again every round was most of
-        // the step's L2 requests, which bound it (16 a cycle on an XCD).
+        // the step's L2 requests.
         // Then two edges at a time of both vertices, in one read each.
         int32_t dy[U], m[U], p[U];
         bool act[U], lead[U];  // lead: every edge before p has a fixed tail

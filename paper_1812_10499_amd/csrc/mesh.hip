@@ -5,17 +5,17 @@
 // (13 of 18 us a round on a 1024 x 1024 grid), the grid-wide kernel by its
 // barriers and list windows.  Here a round takes 4.8 us: the chain of atomic,
 // mailbox, word, D, vertex record, in-edges and C, each through the L2 or the
-// Infinity Cache, one after another in some wave of every round (relax 2.5,
-// waiting for the words 2.8, D and C 1.5, newcomers 2.3, fix 2.1, last wait
-// 0.7 thousand cycles).  1024 x 1024 grid 80 -> 22.4 ms, 2048 x 2048 372 ->
+// Infinity Cache, one after another in some wave of every round (relax 2.2,
+// waiting for the words 2.7, D and C 1.9, newcomers 2.6, fix 2.5, last wait
+// 0.5 thousand cycles).  1024 x 1024 grid 80 -> 22.4 ms, 2048 x 2048 372 ->
 // 78, 64 solves of a 512 x 512 grid 9.7 -> 7.5.
 //
 // Every vertex belongs to one wave of the team (a hash of its id).  An open
 // vertex lives in a seat in its wave's registers from its discovery to its
 // fix, with its lower bound, offsets and lightest in-edges, so a round reads
 // only D and the tails' C for it.  What the waves share goes through
-// agent-scope relaxed atomics and nothing else (D, C, the mailboxes, the
-// words below), so no cache is written back or invalidated, wherever the
+// agent-scope relaxed loads and atomics and the stores of team.h and nothing else
+// (D, C, the mailboxes, the words below), so no cache is written back or invalidated, wherever the
 // waves run; the blocks are numbered so that a team shares an XCD's L2.
 //
 // A round of wave w:
