@@ -406,7 +406,9 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
  * every setting.  A zero field takes the default.
  *   blocks:      grid size, 1 .. the co-resident maximum (default: that
  *                maximum, one 1024-thread block per compute unit, and half
- *                of it for a single solve on at most 6291456 edges);
+ *                of it for a single solve on at most 6291456 edges, except
+ *                under C scope ALL on more than 327680 vertices none of
+ *                which has edges to or from a 64th of them);
  *   solo_edges:  a phase with at most this many edges runs on one block
  *                with block barriers only (default 8192; negative: never);
  *   block_units: otherwise the phase runs on about (work units) /
@@ -420,13 +422,14 @@ sssp_status sssp_backward(const sssp_csr *graphs, int32_t num_graphs, const int3
  *                `blocks` workgroups at a time): 0 (default) when every
  *                graph has low degree spread (deg_max * n < 3m: many small
  *                rounds), 1 always, negative never.  By default, few
- *                instances (at most half as many as compute units) run each
- *                in a team of cooperating workgroups instead; one whose open
- *                set outgrows its team runs again in one workgroup.  Also by
- *                default, solves whose graphs all run C scope ALL and have
- *                no vertex of more than 256 edges run in teams of workgroups
- *                that own every vertex (a non-zero wg: on the grid-wide
- *                kernel).
+ *                instances (at most half as many as compute units; at most
+ *                32 where a graph has more than 4 edges a vertex, none above
+ *                16) run each in a team of cooperating workgroups instead;
+ *                one whose open set outgrows its team goes on in one
+ *                workgroup.  Also by default, solves whose graphs all run C
+ *                scope ALL and have no vertex of more than 256 edges run in
+ *                teams of workgroups that own every vertex (a non-zero wg:
+ *                on the grid-wide kernel).
  */
 typedef struct {
   int32_t blocks;
