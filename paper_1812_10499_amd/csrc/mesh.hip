@@ -13,10 +13,10 @@
 // Every vertex belongs to one wave of the team (a hash of its id).  An open
 // vertex lives in a seat in its wave's registers from its discovery to its
 // fix, with its lower bound, offsets and lightest in-edges, so a round reads
-// only D and the tails' C for it.  What the waves share goes through
-// agent-scope relaxed loads and atomics and the stores of team.h and nothing else
-// (D, C, the mailboxes, the words below), so no cache is written back or invalidated, wherever the
-// waves run; the blocks are numbered so that a team shares an XCD's L2.
+// only D and the tails' C for it.  What the waves share (D, C, the mailboxes,
+// the words below) goes through agent-scope relaxed loads and atomics and the
+// stores of team.h and nothing else, so no cache is written back or invalidated,
+// wherever the waves run; the blocks are numbered so that a team shares an XCD's L2.
 //
 // A round of wave w:
 //   relax the edges of its relax set; a first discovery goes to the owner's
@@ -263,7 +263,8 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
             if (od == V::INF) {  // a first discovery
               const int o = mesh_owner(er.x, lw);
               const int p = atomicAdd(&s.sent[o], 1);
-              if (__builtin_expect(p < kBox, 1)) put64(&box[((size_t)o * kBox + p) * W + w], tagged(ep, er.x), same);
+              if (__builtin_expect(p < kBox, 1))
+                put64(&box[((size_t)o * kBox + p) * W + w], tagged(ep, er.x), same);
               else full = true;
             }
           }
@@ -528,10 +529,10 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
 // 165, 244.  16 solves of a 66 x 66 grid 938, 897, 913, 1119, 64 of them 979,
 // 994, 1045, 1132.  Wide graphs get all there is room for: 32 solves of 5000
 // vertices 8-regular on 16 and 32 waves 437 and 303, 395 in one workgroup each.
-// At most 64 (a lane reads one wave's words; a 1024 x 1024 grid
-// takes 22.4 ms on 64, 27.8 on 32).  All teams together kMeshWavesPerCu waves per compute unit: 64 solves of a 384 x
-// 384 grid take 4.8 ms at 8, 5.3 at 4 and 11.5 at 2 (seats fill up), 5.8 in
-// one workgroup each.
+// At most 64 (a lane reads one wave's words; a 1024 x 1024 grid takes 22.4 ms on
+// 64, 27.8 on 32).  All teams together kMeshWavesPerCu waves per compute unit: 64
+// solves of a 384 x 384 grid take 4.8 ms at 8, 5.3 at 4 and 11.5 at 2 (seats fill
+// up), 5.8 in one workgroup each.
 constexpr int32_t kMeshPerWave = 512;
 constexpr int kMeshRoomy = 512;
 // Wide graphs: four seats a lane, and beyond this many instances, whose teams
