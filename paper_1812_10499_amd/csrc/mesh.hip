@@ -522,19 +522,24 @@ __global__ __launch_bounds__(SSSP_WAVE) void mesh_rounds_kernel(RoundArgs a, Mes
 }
 
 // Waves per team: one per kMeshPerWave vertices, and more while all teams
-// together have at most kMeshRoomy (two a compute unit): they hold wider open
-// sets, and cost nothing.  Single solves on 8, 16, 32 waves and in one
+// together have at most kMeshRoomy (six a compute unit): they hold wider open
+// sets, and cost little.  Single solves on 8, 16, 32 waves and in one
 // workgroup: 70 x 70 grid 733, 694, 675, 883 us; 20^3 mesh 936 (gives up), 564,
 // 482, 723; random 3-regular on 5000 vertices 333 (gives up), 352 (gives up),
-// 165, 244.  16 solves of a 66 x 66 grid 938, 897, 913, 1119, 64 of them 979,
-// 994, 1045, 1132.  Wide graphs get all there is room for: 32 solves of 5000
-// vertices 8-regular on 16 and 32 waves 437 and 303, 395 in one workgroup each.
+// 165, 244.  48 solves: 66 x 66 grid 973, 965, 998, 1104, 96 x 96 1500, 1476,
+// 1505, 1730, 3-regular on 5000 vertices 369, 355, 299, 303, on 9000 556, 534, 493,
+// 484.  64: 977, 1002, 1060, 1116; 1515, 1524, 1566, 1736; 369, 356, 316, 304; 570,
+// 558, 518, 500.  (Whether an open set will fit cannot be told beforehand: small
+// graphs without a planar grid's structure lose up to a fourth from 49 instances
+// on, grids gain a tenth to a third.)  Wide graphs get all there is room for: 32
+// solves of 5000 vertices 8-regular on 16 and 32 waves 437 and 303, 395 in one
+// workgroup each.
 // At most 64 (a lane reads one wave's words; a 1024 x 1024 grid takes 22.4 ms on
 // 64, 27.8 on 32).  All teams together kMeshWavesPerCu waves per compute unit: 64
 // solves of a 384 x 384 grid take 4.8 ms at 8, 5.3 at 4 and 11.5 at 2 (seats fill
 // up), 5.8 in one workgroup each.
 constexpr int32_t kMeshPerWave = 512;
-constexpr int kMeshRoomy = 512;
+constexpr int kMeshRoomy = 1536;
 // Wide graphs: four seats a lane, and beyond this many instances, whose teams
 // would be small, a workgroup each.  Against one workgroup each (and two seats):
 // one 50^3 mesh 11.3 -> 3.4 ms (6.9), 15^4 5.3 -> 1.4 (4.5), 5000 vertices
